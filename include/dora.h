@@ -404,7 +404,7 @@ typedef struct {
  *              valid images.
  *   B 1 .. 2^24.
  * Returns DORA_OK or a negative dora_status (DORA_ERR_SHAPE for a config
- * field out of range); enqueues one single-workgroup kernel.
+ * field out of range); enqueues one kernel (two past 1024 images).
  */
 int dora_trajectory_flops(const int32_t* tokens, int32_t B, const dora_flops_config* config, int64_t* flops_out,
                           int64_t* total_out, int32_t* dev_status, void* stream);

@@ -58,3 +58,22 @@ def test_invalid_rows(gpu):
     assert int(st.item()) & gpu.DORA_DEV_KEEP_RANGE
     assert np.all(f[1:4] == -1) and np.array_equal(f[[0, 4, 5]], want[[0, 4, 5]])
     assert int(tot.item()) == int(want[[0, 4, 5]].sum())
+
+
+@pytest.mark.parametrize("B", [1, 1023, 1024, 1025, 2500])
+@pytest.mark.parametrize("L", [1, 7, 8, 9, 24])
+def test_group_and_load_edges(gpu, B, L):
+    """Around the switch to several workgroups (1024 images) and the eight counts
+    loaded at once, twice into the same total, with an invalid last image."""
+    d, N0, p = 192, 196, 16
+    M = (N0 - 4) // 2
+    T = trajectories(np.random.default_rng(100 * L + B), B, L, N0, M)
+    T[L, B - 1] = 0
+    want = oracle.trajectory_flops(T[:, :B - 1], d, L, N0, p, M) if B > 1 else np.zeros(0, np.int64)
+    total = torch.full((1,), 12345, dtype=torch.int64, device="cuda")
+    for _ in range(2):
+        f, tot, st = gpu.dora_trajectory_flops(to_dev(T), d, N0, p, total_out=total)
+        torch.cuda.synchronize()
+        f = f.cpu().numpy()
+        assert int(st.item()) == gpu.DORA_DEV_KEEP_RANGE
+        assert f[B - 1] == -1 and np.array_equal(f[:B - 1], want) and int(tot.item()) == int(want.sum())
