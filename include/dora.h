@@ -421,7 +421,9 @@ int dora_trajectory_flops(const int32_t* tokens, int32_t B, const dora_flops_con
  *   softmax_scale  <= 0 selects 1/sqrt(D).
  *   dtype      DORA_BF16: bf16 inputs, fp32 accumulation and softmax, P rounded
  *              to bf16 for the P.V product, output rounded once to bf16.
- *              DORA_F32: fp32 throughout.
+ *              DORA_F32: fp32 throughout (products from three-term bf16
+ *              splits of the operands, to within 2^-26; infinities and NaN as
+ *              in fp32 arithmetic).
  *   workspace  as filled by dora_varlen_attn_plan (or dora_select_pack_plan)
  *              with the same cu_seqlens, B, H, max_seqlen and total; otherwise
  *              DORA_DEV_PLAN is set and nothing is written.

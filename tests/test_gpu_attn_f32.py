@@ -1,0 +1,93 @@
+"""fp32 attention from split bf16 products (GPU): tile, stage and part edges on
+both launch forms, and values that the split cannot represent."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from gpu_util import cu_of, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# One rounding of fp32 sums is 6e-8 of the result; scores carry an absolute
+# error of about 64 roundings of |q||k| / 64 <= 64 * 6e-8 * 2, so each weight
+# is within 8e-6 of its value relatively, and the output of its rms.
+REL = 1e-5
+LENS = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 97, 128, 129, 160, 161, 191, 192, 193, 224, 225, 400]
+
+
+def run(gpu, q, k, v, lens):
+    cu = cu_of(lens)
+    out = gpu.dora_varlen_attn(to_dev(q), to_dev(k), to_dev(v), to_dev(cu), int(max(lens)))
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64), cu
+
+
+def close(got, want, what=""):
+    rms = np.sqrt((want ** 2).mean())
+    assert np.all(np.isfinite(got)), what
+    assert np.abs(got - want).max() <= REL * max(rms, np.abs(want).max() / 16), (what, np.abs(got - want).max(), rms)
+
+
+# heads * sequences * 3 chunks: 23 * 12 items and more, or 1 * 3 a call (split while 3 items per workgroup fit)
+@pytest.mark.parametrize("H", [1, 12])
+def test_edges(gpu, H):
+    rng = np.random.default_rng(H)
+    groups = [LENS] if H > 1 else [LENS[i:i + 4] for i in range(0, len(LENS), 4)]
+    for lens in groups:
+        q, k, v = workloads.random_qkv(rng, lens, H, "f32")
+        got, cu = run(gpu, q, k, v, lens)
+        close(got, oracle.varlen_attn(q, k, v, cu, "f32"), lens)
+
+
+@pytest.mark.parametrize("n", [40, 210])
+@pytest.mark.parametrize("B", [1, 64])
+def test_values_past_the_split(gpu, n, B):
+    """Infinities, NaN and the largest values give what fp32 arithmetic gives;
+    V near the smallest normal numbers keeps its relative precision."""
+    H, lens = 2, [n] * B
+    rng = np.random.default_rng(n + B)
+    q0, k0, v0 = workloads.random_qkv(rng, lens, H, "f32")
+    b, j = B - 1, n - 3                       # the row of the last sequence that is changed
+    row = b * n + j
+
+    # a key of score -inf has weight 0: the sequence without it
+    q, k = q0.copy(), k0.copy()
+    q[:, 0, 0] = 1.0
+    k[row, 0, 0] = -np.inf
+    got, _ = run(gpu, q, k, v0, lens)
+    keep = np.delete(np.arange(b * n, b * n + n), j)
+    sub, cu = [np.ascontiguousarray(t[keep]) for t in (k, v0)], cu_of([n - 1])
+    want = oracle.varlen_attn(np.ascontiguousarray(q[keep]), *sub, cu, "f32")
+    close(got[keep][:, 0], want[:, 0])
+
+    # one infinite, one NaN and one huge value in V reach their own dimensions only
+    v, vz = v0.copy(), v0.copy()
+    for d, x in ((3, np.inf), (5, np.nan), (9, np.finfo(np.float32).max)):
+        v[row, 1, d], vz[row, 1, d] = x, 0.0
+    got, cu = run(gpu, q0, k0, v, lens)
+    want = oracle.varlen_attn(q0, k0, vz, cu, "f32")
+    seq = slice(b * n, b * n + n)
+    assert np.all(got[seq, 1, 3] == np.inf) and np.all(np.isnan(got[seq, 1, 5]))
+    one = np.zeros_like(v0)
+    one[row, 1, 9] = 1.0
+    weight = oracle.varlen_attn(q0, k0, one, cu, "f32")[seq, 1, 9] * np.float64(np.finfo(np.float32).max)
+    assert np.abs(got[seq, 1, 9] / weight - 1).max() <= REL
+    got[seq, 1, [[3], [5], [9]]] = want[seq, 1, [[3], [5], [9]]] = 0.0
+    close(got, want)
+
+    # a NaN query spoils its own row only
+    q = q0.copy()
+    q[row, 0, 7] = np.nan
+    got, cu = run(gpu, q, k0, v0, lens)
+    want = oracle.varlen_attn(q0, k0, v0, cu, "f32")
+    assert np.all(np.isnan(got[row, 0]))
+    got[row, 0] = want[row, 0] = 0.0
+    close(got, want)
+
+    # tiny and large V
+    for scale in (2.0 ** -115, 2.0 ** 90, 2.0 ** 120):
+        v = v0 * np.float32(scale)
+        got, cu = run(gpu, q0, k0, v, lens)
+        close(got / scale, oracle.varlen_attn(q0, k0, v0, cu, "f32"), scale)
