@@ -22,7 +22,7 @@
 //   all waves     longer rows: the four waves each hold a quarter of the
 //                 positions and select by 8-bit digits together (LDS
 //                 histograms, a barrier per digit), then compact in order.
-//   all waves     16-byte row copies, 2 loads in flight per lane.
+//   all waves     16-byte row copies, 8 loads in flight per lane.
 //
 // dora_select_pack_plan also writes the attention work queue of the packed
 // output (Sec. 3.5 "Inference": one sequence per image, keep[b] rows): it
@@ -31,7 +31,8 @@
 // longer sequences first, then lower image index), and workgroup (0, 0)
 // writes the plan header.
 #include <limits.h>
-#include <stdlib.h>
+
+#include <algorithm>
 
 #include "dora_internal.h"
 
@@ -40,7 +41,12 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kDigitSelectSlots = 8;  // rows of more than 256 tokens select by 8-bit digits
-constexpr int kCopyUnroll = 2;  // loads in flight per lane: few, so stores start early (measured best)
+// 16-byte loads in flight per lane of the copy (half as many rows of two
+// operands in the residual variant).  Inputs rotating through more than the
+// last-level cache holds, 2 -> 8 loads at the split below: 8192 images of 197
+// rows of 1536 bytes 626 -> 602 us, 1024 images 81.1 -> 78.8, 256 images 25.1
+// -> 25.1; residual 1024 images 124 -> 120, 256 images 36.5 -> 34.7.
+constexpr int kCopyLoads = 8;
 // Up to this many images each workgroup sums keep[0..b) itself (at most 8 KB
 // of keep counts from the L2, cheaper than a second launch); above it one
 // workgroup scans the keep counts into cu_out first.
@@ -249,6 +255,7 @@ __device__ __forceinline__ u32x4 combine(uint4 x, uint4 y) {
 
 template <int SLOTS, int MODE>
 __device__ __forceinline__ void select_pack_body(const SelectPackParams& p) {
+  constexpr int kCopyUnroll = MODE == kCopy ? kCopyLoads : kCopyLoads / 2;
   // Rows of more than 256 tokens are selected by all four waves, a quarter
   // of the positions each (kWide); shorter rows by wave 0 alone.
   constexpr bool kWide = SLOTS >= kDigitSelectSlots;
@@ -575,8 +582,18 @@ hipError_t launch(const SelectPackParams& p, int mode, hipStream_t stream) {
   return hipGetLastError();
 }
 
-int pick_split(int B, int N) {
-  int split = (1024 + B - 1) / B;  // ~4 workgroups per compute unit
+// Workgroups per image: about 48 KB of the image's rows each, at most 8, so
+// that the selection of one workgroup runs under the copies of others and the
+// last round of workgroups is short; more where the batch alone would leave
+// the chip idle (about 4 workgroups per compute unit).  Cold inputs, 1 / 2 / 4
+// / 6 / 8 workgroups per image: 8192 images of 303 KB 675 / 659 / 642 / 602 /
+// 608 us, 1024 of 303 KB 92.6 / 87.4 / 81.1 / 78.8 / 78.2, 256 of 886 KB 72.7 /
+// 71.9 / 68.7 / 68.6 / 66.5, 8192 of 76 KB 171 / 157 / 180 / 250 / 323, 4096 of
+// 25 KB 33.5 / 41.2 / 65 (each workgroup repeats the selection).
+int pick_split(int B, int N, int64_t row_bytes) {
+  constexpr int64_t kPiece = 48 << 10;
+  const int by_bytes = static_cast<int>(std::min<int64_t>((N * row_bytes + kPiece / 2) / kPiece, 8));
+  int split = std::max((1024 + B - 1) / B, by_bytes);
   const int max_split = N / 16 > 1 ? N / 16 : 1;  // at least ~16 rows per workgroup
   if (split > max_split) split = max_split;
   if (split < 1) split = 1;
@@ -607,7 +624,7 @@ int prepare(const float* scores, const int32_t* keep, const void* tokens, const 
   p->B = B;
   p->N = N;
   p->row_vecs = static_cast<int32_t>(row_bytes / 16);
-  p->split = pick_split(B, N);
+  p->split = pick_split(B, N, row_bytes);
   p->idx_out = idx_out;
   p->cu_out = cu_out;
   p->packed = static_cast<uint4*>(packed_out);
