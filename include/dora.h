@@ -166,7 +166,7 @@ int dora_varlen_attn_plan(const int32_t* cu_seqlens, int32_t B, int32_t H, int32
  * in the select/pack launch while the rows are copied (it depends on the
  * keep counts only), its items ordered by decreasing keep count, then by
  * image.  Past 2048 images the keep counts are first scanned into cu_out by
- * a one-workgroup launch and the plan is made from cu_out as
+ * a one-workgroup launch and the plan is made from cu_out, beside the copy, as
  * dora_varlen_attn_plan makes it (decreasing length, equal lengths in an
  * unspecified order); attention results do not depend on that order.
  *
@@ -178,7 +178,7 @@ int dora_varlen_attn_plan(const int32_t* cu_seqlens, int32_t B, int32_t H, int32
  *              keep[b] is outside [1, max_seqlen] or sum(keep) > total (the
  *              plan is then empty and execute writes nothing).
  *
- * Returns DORA_OK or a negative dora_status; enqueues one kernel (three
+ * Returns DORA_OK or a negative dora_status; enqueues one kernel (two
  * past 2048 images).
  */
 int dora_select_pack_plan(const float* scores, const int32_t* keep, const void* tokens,

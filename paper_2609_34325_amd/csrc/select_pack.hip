@@ -34,6 +34,7 @@
 
 #include <algorithm>
 
+#include "attn_plan.h"
 #include "dora_internal.h"
 
 namespace dora {
@@ -254,7 +255,7 @@ __device__ __forceinline__ u32x4 combine(uint4 x, uint4 y) {
 }
 
 template <int SLOTS, int MODE>
-__device__ __forceinline__ void select_pack_body(const SelectPackParams& p) {
+__device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int block) {
   constexpr int kCopyUnroll = MODE == kCopy ? kCopyLoads : kCopyLoads / 2;
   // Rows of more than 256 tokens are selected by all four waves, a quarter
   // of the positions each (kWide); shorter rows by wave 0 alone.
@@ -274,8 +275,8 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int b = blockIdx.x / p.split;
-  const int s = blockIdx.x - b * p.split;
+  const int b = block / p.split;
+  const int s = block - b * p.split;
 
   // Segment of image b in the input.
   long long off_in, n;
@@ -311,7 +312,7 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p) {
   // With a plan, workgroup (b, 0) writes image b's attention items and
   // workgroup (0, 0) the plan header.
   const bool plan_img = p.plan_hdr != nullptr && s == 0;
-  const bool plan_head = p.plan_hdr != nullptr && blockIdx.x == 0;
+  const bool plan_head = p.plan_hdr != nullptr && block == 0;
 
   // Waves 1-3: output offset of image b, keep[0] + ... + keep[b-1].  For the
   // plan (queue order: longer sequences first, then lower index), b's class
@@ -507,12 +508,22 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p) {
 // residual variant writes h + a of each kept row.
 template <int SLOTS>
 __global__ __launch_bounds__(kThreads) void select_pack_kernel(SelectPackParams p) {
-  select_pack_body<SLOTS, kCopy>(p);
+  select_pack_body<SLOTS, kCopy>(p, blockIdx.x);
+}
+
+// Large batches with a plan: the first workgroup makes the plan from cu_out
+// (written by the launch before) while the others copy.  8192 images of 1536-
+// byte rows: a plan launch of its own took 55 us before a copy of 600.
+template <int SLOTS>
+__global__ __launch_bounds__(kThreads) void select_pack_planning_kernel(SelectPackParams p, PlanParams plan) {
+  __shared__ PlanLds<kThreads> lds;
+  if (blockIdx.x == 0) attn_plan_body<kThreads>(plan, lds);
+  else select_pack_body<SLOTS, kCopy>(p, static_cast<int>(blockIdx.x) - 1);
 }
 
 template <int SLOTS, int MODE>
 __global__ __launch_bounds__(kThreads) void select_pack_residual_kernel(SelectPackParams p) {
-  select_pack_body<SLOTS, MODE>(p);
+  select_pack_body<SLOTS, MODE>(p, blockIdx.x);
 }
 
 __device__ __forceinline__ long long wave_inclusive_scan64(long long v, int lane) {
@@ -571,9 +582,11 @@ __global__ __launch_bounds__(kScanThreads) void keep_scan_kernel(const int32_t* 
 }
 
 template <int SLOTS>
-hipError_t launch(const SelectPackParams& p, int mode, hipStream_t stream) {
+hipError_t launch(const SelectPackParams& p, const PlanParams* plan, int mode, hipStream_t stream) {
   const dim3 grid(p.B * p.split), block(kThreads);
-  if (mode == kAddBf16)
+  if (plan != nullptr)
+    hipLaunchKernelGGL(select_pack_planning_kernel<SLOTS>, dim3(p.B * p.split + 1), block, 0, stream, p, *plan);
+  else if (mode == kAddBf16)
     hipLaunchKernelGGL((select_pack_residual_kernel<SLOTS, kAddBf16>), grid, block, 0, stream, p);
   else if (mode == kAddF32)
     hipLaunchKernelGGL((select_pack_residual_kernel<SLOTS, kAddF32>), grid, block, 0, stream, p);
@@ -641,25 +654,27 @@ int prepare(const float* scores, const int32_t* keep, const void* tokens, const 
 int launch_select_pack(SelectPackParams p, void* stream, int mode = kCopy) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t err;
+  PlanParams plan{};
+  bool planning = false;
   if (p.B > kFusedScanMaxB) {
-    // Large batch: the block scan writes cu_out first; a plan is then built
-    // from cu_out by the attention plan kernel (sequences of at least one row).
+    // Large batch: the block scan writes cu_out first; a plan is then made
+    // from cu_out beside the copy (sequences of at least one row).
     hipLaunchKernelGGL(keep_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, p.keep, p.B, p.cu_out);
     if (hipGetLastError() != hipSuccess) return DORA_ERR_HIP;
     if (p.plan_hdr != nullptr) {
-      const int rc = launch_attn_plan(p.cu_out, p.B, p.H, p.max_seqlen, p.plan_total, 1, p.plan_hdr, p.status, stream);
-      if (rc != DORA_OK) return rc;
+      plan = make_plan_params(p.cu_out, p.B, p.H, p.max_seqlen, p.plan_total, 1, p.plan_hdr, p.status);
+      planning = true;
       p.plan_hdr = nullptr;
       p.plan_items = nullptr;
     }
     p.cu_ready = 1;
   }
-  if (p.N <= 64) err = launch<1>(p, mode, st);
-  else if (p.N <= 128) err = launch<2>(p, mode, st);
-  else if (p.N <= 256) err = launch<4>(p, mode, st);
-  else if (p.N <= 512) err = launch<8>(p, mode, st);
-  else if (p.N <= 1024) err = launch<16>(p, mode, st);
-  else err = launch<32>(p, mode, st);
+  if (p.N <= 64) err = launch<1>(p, planning ? &plan : nullptr, mode, st);
+  else if (p.N <= 128) err = launch<2>(p, planning ? &plan : nullptr, mode, st);
+  else if (p.N <= 256) err = launch<4>(p, planning ? &plan : nullptr, mode, st);
+  else if (p.N <= 512) err = launch<8>(p, planning ? &plan : nullptr, mode, st);
+  else if (p.N <= 1024) err = launch<16>(p, planning ? &plan : nullptr, mode, st);
+  else err = launch<32>(p, planning ? &plan : nullptr, mode, st);
   return err == hipSuccess ? DORA_OK : DORA_ERR_HIP;
 }
 

@@ -39,6 +39,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "attn_plan.h"
 #include "dora_internal.h"
 
 namespace dora {
@@ -55,19 +56,7 @@ constexpr int kKRes = 256;             // keys resident in LDS per stage (bf16)
 // query tiles of an item, so the queue's latency lands where there is slack.
 constexpr int kQueueThread = kThreads - 64;
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanMaxChunks = (DORA_MAX_SEQLEN + kAttnQTile - 1) / kAttnQTile;  // chunks of the longest sequence
-constexpr int kPlanBins = 1024;
 constexpr float kLog2e = 1.4426950408889634f;
-
-struct PlanParams {
-  const int32_t* cu;
-  int32_t B, H, max_seqlen;
-  int32_t min_len;  // shortest valid sequence (0; 1 for the plan of a select/pack output)
-  int64_t total;
-  AttnPlanHeader* hdr;
-  int2* items;
-  int32_t* status;
-};
 
 struct AttnParams {
   const void* q;
@@ -85,132 +74,9 @@ struct AttnParams {
 
 // ------------------------------- plan -------------------------------------
 
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int t = __shfl_up(v, off, 64);
-    if (lane >= off) v += t;
-  }
-  return v;
-}
-
-// Exclusive scan of one value per thread across the 1024-thread block.
-__device__ int block_exclusive_scan(int v, int* wave_sums, int* total) {
-  constexpr int kW = kPlanThreads / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int incl = wave_inclusive_scan(v);
-  if (lane == 63) wave_sums[wave] = incl;
-  __syncthreads();
-  if (wave == 0) {
-    const int x = lane < kW ? wave_sums[lane] : 0;
-    const int xi = wave_inclusive_scan(x);
-    if (lane < kW) wave_sums[lane] = xi - x;
-    if (lane == kW - 1) wave_sums[kW] = xi;
-  }
-  __syncthreads();
-  const int r = incl - v + wave_sums[wave];
-  *total = wave_sums[kW];
-  __syncthreads();
-  return r;
-}
-
 __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(PlanParams p) {
-  __shared__ int32_t s_cu[kPlanMaxB + 1];  // cu_seqlens, read from global memory once
-  __shared__ int hist[kPlanBins];
-  __shared__ uint32_t order[kPlanMaxB];  // sequence | len << 13, by decreasing length
-  __shared__ int base[kPlanMaxB + 1];    // first item of each sorted position
-  __shared__ int wave_sums[kPlanThreads / 64 + 1];
-  __shared__ int cls_lo[kPlanMaxChunks + 1], cls_hi[kPlanMaxChunks + 1];  // class bounds by chunk count
-  __shared__ int s_bad;
-  const int tid = threadIdx.x;
-  // Length bins: bin 0 for empty sequences, then (len - 1) >> shift + 1.
-  // The smallest shift that fits is at most 5 (max_seqlen <= 16384), and
-  // 2^shift divides kAttnQTile, so a bin never straddles a chunk boundary and
-  // the sequences of equal chunk count stay contiguous in the sorted order.
-  int shift = 0;
-  while (((p.max_seqlen - 1) >> shift) + 1 >= kPlanBins) ++shift;
-  auto bin_of = [shift](int len) { return len == 0 ? 0 : ((len - 1) >> shift) + 1; };
-
-  for (int i = tid; i < kPlanBins; i += kPlanThreads) hist[i] = 0;
-  for (int i = tid; i <= p.B; i += kPlanThreads) s_cu[i] = p.cu[i];
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
-  for (int b = tid; b < p.B; b += kPlanThreads) {
-    const long long a = s_cu[b], e = s_cu[b + 1];
-    const long long len = e - a;
-    if (a < 0 || e > p.total || len < p.min_len || len > p.max_seqlen || (b == 0 && a != 0)) s_bad = 1;
-    else atomicAdd(&hist[bin_of(static_cast<int>(len))], 1);
-  }
-  __syncthreads();
-  if (s_bad) {
-    if (tid == 0) {
-      atomicOr(p.status, DORA_DEV_CU_SEQLENS);
-      write_plan_header(p.hdr, 0, p.B, p.H, p.max_seqlen, p.total);
-    }
-    return;
-  }
-
-  // Counting sort by length, longest first.
-  {
-    const int bin = kPlanBins - 1 - tid;
-    int unused;
-    const int start = block_exclusive_scan(hist[bin], wave_sums, &unused);
-    hist[bin] = start;
-  }
-  __syncthreads();
-  for (int b = tid; b < p.B; b += kPlanThreads) {
-    const int len = s_cu[b + 1] - s_cu[b];
-    const int pos = atomicAdd(&hist[bin_of(len)], 1);
-    order[pos] = static_cast<uint32_t>(b) | (static_cast<uint32_t>(len) << 13);
-  }
-  __syncthreads();
-
-  // Items per sorted position, then their offsets.
-  const int per = (p.B + kPlanThreads - 1) / kPlanThreads;
-  int local = 0;
-  for (int i = 0; i < per; ++i) {
-    const int pos = tid * per + i;
-    if (pos < p.B) local += p.H * attn_chunks(static_cast<int>(order[pos] >> 13));
-  }
-  int n_items;
-  int run = block_exclusive_scan(local, wave_sums, &n_items);
-  for (int i = 0; i < per; ++i) {
-    const int pos = tid * per + i;
-    if (pos < p.B) {
-      base[pos] = run;
-      run += p.H * attn_chunks(static_cast<int>(order[pos] >> 13));
-    }
-  }
-  if (tid == 0) base[p.B] = n_items;
-  __syncthreads();
-
-  // Class bounds: sorted positions [cls_lo[ch], cls_hi[ch]) hold the
-  // sequences of ch chunks (chunk counts fall with position).
-  auto chunks_at = [&](int pos) { return attn_chunks(static_cast<int>(order[pos] >> 13)); };
-  for (int pos = tid; pos < p.B; pos += kPlanThreads) {
-    const int ch = chunks_at(pos);
-    if (pos == 0 || chunks_at(pos - 1) != ch) cls_lo[ch] = pos;
-    if (pos == p.B - 1 || chunks_at(pos + 1) != ch) cls_hi[ch] = pos + 1;
-  }
-  __syncthreads();
-  // Emit, one sorted position per thread at a time: its H x chunks items go
-  // to their slots in the class (attn_item_slot).
-  for (int pos = tid; pos < p.B; pos += kPlanThreads) {
-    const uint32_t o = order[pos];
-    const int b = static_cast<int>(o & 0x1FFFu);
-    const int len = static_cast<int>(o >> 13);
-    const int ch = attn_chunks(len);
-    if (ch == 0) continue;
-    const int c0 = cls_lo[ch];
-    const int groups = (cls_hi[ch] - c0) * p.H;
-    const long long cbase = base[c0];
-    for (int h = 0; h < p.H; ++h)
-      for (int c = 0; c < ch; ++c)
-        p.items[attn_item_slot(cbase, groups, ch, (pos - c0) * p.H + h, c)] = encode_item(s_cu[b], len, h, c);
-  }
-  if (tid < 32) p.hdr->zero_row[tid] = 0u;
-  if (tid == 0) write_plan_header(p.hdr, n_items, p.B, p.H, p.max_seqlen, p.total);
+  __shared__ PlanLds<kPlanThreads> lds;
+  attn_plan_body<kPlanThreads>(p, lds);
 }
 
 // ------------------------------ execute -----------------------------------
@@ -1454,23 +1320,6 @@ int device_cu_count(int* device_out) {
   return n;
 }
 
-int launch_attn_plan(const int32_t* cu, int32_t B, int32_t H, int32_t max_seqlen, int64_t total, int32_t min_len,
-                     void* workspace, int32_t* dev_status, void* stream) {
-  const AttnWorkspaceLayout L = attn_workspace_layout(B, H, max_seqlen);
-  PlanParams p;
-  p.cu = cu;
-  p.B = B;
-  p.H = H;
-  p.max_seqlen = max_seqlen;
-  p.min_len = min_len;
-  p.total = total;
-  p.status = dev_status;
-  p.hdr = static_cast<AttnPlanHeader*>(workspace);
-  p.items = reinterpret_cast<int2*>(static_cast<char*>(workspace) + L.items_off);
-  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, static_cast<hipStream_t>(stream), p);
-  return hipGetLastError() == hipSuccess ? DORA_OK : DORA_ERR_HIP;
-}
-
 }  // namespace dora
 
 extern "C" size_t dora_varlen_attn_workspace_size(int32_t B, int32_t H, int32_t max_seqlen) {
@@ -1488,7 +1337,9 @@ extern "C" int dora_varlen_attn_plan(const int32_t* cu_seqlens, int32_t B, int32
   const AttnWorkspaceLayout L = attn_workspace_layout(B, H, max_seqlen);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < L.bytes)
     return DORA_ERR_WORKSPACE;
-  return launch_attn_plan(cu_seqlens, B, H, max_seqlen, total, 0, workspace, dev_status, stream);
+  const PlanParams p = make_plan_params(cu_seqlens, B, H, max_seqlen, total, 0, workspace, dev_status);
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, static_cast<hipStream_t>(stream), p);
+  return hipGetLastError() == hipSuccess ? DORA_OK : DORA_ERR_HIP;
 }
 
 extern "C" int dora_varlen_attn_execute(const void* q, const void* k, const void* v,

@@ -275,3 +275,54 @@ def test_fused_plan_large_batch_errors(gpu, case):
     assert st & want_bits == want_bits
     _, n, _ = read_plan(ws)
     assert n == 0
+
+
+@pytest.mark.parametrize("B,max_seqlen,H", [(1, 1, 1), (1, 16384, 12), (63, 1023, 1), (64, 4096, 3), (65, 1000, 16),
+                                            (255, 576, 2), (1023, 1023, 2), (1025, 2048, 1), (2500, 193, 3)])
+def test_plan_edges(gpu, B, max_seqlen, H):
+    """The plan kernel around its lane, wave and workgroup edges, with sequences
+    whose items one lane writes (few) and a wave writes (more than 64), and empty ones."""
+    rng = np.random.default_rng(B + max_seqlen + H)
+    lens = rng.integers(0, max_seqlen + 1, size=B).astype(np.int32)
+    if B <= max_seqlen <= 1023:
+        lens = rng.permutation(max_seqlen + 1)[:B].astype(np.int32)   # a length per bin: one possible order
+    lens[rng.integers(B)] = max_seqlen
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ws, st = gpu.new_workspace(B, H, max_seqlen), gpu.new_status()
+    gpu.dora_varlen_attn_plan(to_dev(cu), H, max_seqlen, int(cu[-1]), ws, st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    hdr, n, items = read_plan(ws)
+    items[:, 1] &= 0xFFFFFFFF                    # 16384 << 17 is bit 31 of an unsigned word
+    want = expected_items(lens, H, max_seqlen)
+    assert n == len(want) and np.all(hdr[32:64] == 0) and np.all(hdr[QUEUE_INTS + [EXIT_INT]] == 0)
+    if len(set(lens.tolist())) == B and max_seqlen <= 1023:
+        assert np.array_equal(items, want)
+    assert np.all(np.diff([n_chunks(k) for k in (items[:, 1] >> 17)]) <= 0)
+    assert sorted(map(tuple, items.tolist())) == sorted(map(tuple, want.tolist()))
+    assert_groups_share_a_subqueue(items)
+
+
+@pytest.mark.parametrize("B,N", [(2049, 300), (2300, 20)])
+def test_plan_beside_the_copy(gpu, B, N):
+    """Past 2048 images one workgroup of the copy launch makes the plan: rows
+    selected by one wave and by four, and the plan against a separate one."""
+    rng = np.random.default_rng(B + N)
+    H = 3
+
+    class R:
+        pass
+    r = R()
+    r.keep = rng.integers(1, N + 1, size=B).astype(np.int32)
+    r.scores = rng.standard_normal((B, N)).astype(np.float32)
+    r.tokens = rng.integers(0, 2 ** 16, size=(B, N, 8)).astype(np.uint16)
+    total = int(r.keep.sum())
+    idx, cu, packed, ws, st = fused(gpu, r, H, N, total)
+    idx_o, cu_o, packed_o, _ = oracle.select_pack(r.scores, r.keep, r.tokens)
+    assert st == 0 and np.array_equal(cu.cpu().numpy(), cu_o)
+    assert np.array_equal(idx[:total].cpu().numpy(), idx_o)
+    assert np.array_equal(to_host_bits(packed[:total]), packed_o)
+    hdr, n, items = read_plan(ws)
+    want = expected_items(r.keep, H, N)
+    assert n == len(want) and sorted(map(tuple, items.tolist())) == sorted(map(tuple, want.tolist()))
+    assert_groups_share_a_subqueue(items)
