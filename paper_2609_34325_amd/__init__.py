@@ -1,9 +1,10 @@
 """DORA deployment hot path on AMD Instinct MI355X (gfx950).
 
-Thin ctypes binding over ``libdora.so`` (C ABI in ``include/dora.h``).  Every
+Thin binding over ``libdora.so`` (C ABI in ``include/dora.h``).  Every
 step of the path runs in the library's HIP kernels; this module only checks
 tensor arguments, allocates outputs with torch when the caller does not pass
-them, and forwards raw device pointers and the current HIP stream.
+them, and forwards raw device pointers and the current HIP stream (through
+``csrc/host_call.cpp``; calls that it leaves out go through ctypes).
 
 DORA (arXiv 2609.34325): hard deletion keeps CLS and the survivors' order
 (Sec. 3.1, Eq. (1)); deployment removes the highest-scoring visual tokens
@@ -23,6 +24,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdora.so")
+HOST_PATH = os.path.join(_HERE, "_host_call.so")
 
 DORA_F32 = 0
 DORA_BF16 = 1
@@ -69,7 +71,40 @@ EXPORTS = (
     "dora_status_string",
 )
 
+# Entry points that host_call.cpp marshals, in its order, with the name and
+# required type of each tensor argument (None: an integer, float or address).
+_F32, _I32, _I64, _ANY = torch.float32, torch.int32, torch.int64, None
+_PACK = (("scores", _F32), ("keep", _I32), ("tokens", _ANY))
+_PACK_OUT = (("idx_out", _I32), ("cu_out", _I32), ("packed_out", _ANY), None)
+_STATUS = (("dev_status", _I32), None)
+_ATTN = (("q", _ANY), ("k", _ANY), ("v", _ANY), ("cu_seqlens", _I32)) + (None,) * 7 + \
+    (("out", _ANY), ("workspace", _ANY), None) + _STATUS
+_ENTRIES = (
+    ("dora_select_pack", _PACK + (("cu_in", _I32),) + (None,) * 5 + _PACK_OUT + _STATUS),
+    ("dora_select_pack_plan", _PACK + (("cu_in", _I32),) + (None,) * 5 + _PACK_OUT + (None,) * 3 +
+     (("workspace", _ANY), None) + _STATUS),
+    ("dora_select_pack_residual", _PACK + (("a", _ANY), ("cu_in", _I32)) + (None,) * 5 + _PACK_OUT + _STATUS),
+    ("dora_actor_gate", (("p_gate", _F32), ("cu_in", _I32), None, None, None, ("on_rank", _I32), ("on_list", _I32),
+                         ("n_on", _I32)) + _STATUS),
+    ("dora_actor_decode", (("budget_logits", _F32), None, None, ("removal_scores", _F32), ("cu_in", _I32), None, None,
+                           None, ("on_rank", _I32), ("keep_out", _I32), ("scores_out", _F32)) + _STATUS),
+    ("dora_pl_sample", (("scores", _F32), ("gumbel", _F32), ("k", _I32), ("cu_in", _I32), None, None, None,
+                        ("order_out", _I32), ("cu_order_out", _I32), ("logprob_out", _F32), None) + _STATUS),
+    ("dora_pl_logprob", (("scores", _F32), ("order", _I32), ("cu_order", _I32), ("cu_in", _I32), None, None, None,
+                         ("logprob_out", _F32)) + _STATUS),
+    ("dora_lc1_readout", (("x", _ANY), ("cu_seqlens", _I32), None, None, None, None, ("gamma", _F32), ("beta", _F32),
+                          None, ("out", _F32), ("workspace", _ANY), None) + _STATUS),
+    ("dora_trajectory_flops", (("tokens", _I32), None, None, ("flops_out", _I64), ("total_out", _I64)) + _STATUS),
+    ("dora_varlen_attn_plan", (("cu_seqlens", _I32), None, None, None, None, ("workspace", _ANY), None) + _STATUS),
+    ("dora_varlen_attn_execute", _ATTN),
+    ("dora_varlen_attn", _ATTN),
+)
+_INDEX = {name: i for i, (name, _) in enumerate(_ENTRIES)}
+
+_OPTIONAL = ("cu_in", "budget_logits", "removal_scores", "scores_out", "workspace")
+
 _lib = None
+_native_call = None
 
 
 class FlopsConfig(ctypes.Structure):
@@ -86,7 +121,7 @@ class DoraError(RuntimeError):
 
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     """Load libdora.so (built in-tree by ``paper_2609_34325_amd.build``)."""
-    global _lib
+    global _lib, _native_call
     if _lib is not None and path is None:
         return _lib
     p = path or LIB_PATH
@@ -118,7 +153,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.dora_lc1_readout_workspace_size.restype = sz
     lib.dora_lc1_readout_workspace_size.argtypes = [i32, i32]
     lib.dora_trajectory_flops.restype = ctypes.c_int
-    lib.dora_trajectory_flops.argtypes = [vp, i32, ctypes.POINTER(FlopsConfig), vp, vp, vp, vp]
+    lib.dora_trajectory_flops.argtypes = [vp, i32, vp, vp, vp, vp, vp]
     lib.dora_varlen_attn_workspace_size.restype = sz
     lib.dora_varlen_attn_workspace_size.argtypes = [i32, i32, i32]
     lib.dora_varlen_attn_plan.restype = ctypes.c_int
@@ -132,9 +167,31 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.dora_varlen_attn_noalloc.argtypes = lib.dora_varlen_attn_execute.argtypes[:12] + [vp, vp]
     lib.dora_status_string.restype = ctypes.c_char_p
     lib.dora_status_string.argtypes = [ctypes.c_int]
+    lib.addresses = tuple(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name, _ in _ENTRIES)
+    if _native_call is None:
+        if not os.path.exists(HOST_PATH):
+            raise RuntimeError(f"{HOST_PATH} not found; build it with `python -m paper_2609_34325_amd.build`")
+        from . import _host_call
+        _native_call = _host_call.call
     if path is None:
         _lib = lib
     return lib
+
+
+def _call(name: str, stream, *args) -> None:
+    """Check the tensors of one entry point and enqueue it on `stream`.  args:
+    every argument but the stream, tensors as they are.  Raises DoraError for
+    a negative status."""
+    lib = _lib or load_library()
+    which = _INDEX[name]
+    st = _stream(stream)
+    rc = _native_call(which, lib.addresses[which], *args, st)
+    if rc is NotImplemented:  # an argument that the native path leaves to these checks
+        spec = _ENTRIES[which][1]
+        rc = getattr(lib, name)(*(a if s is None or (a is None and s[0] in _OPTIONAL) else _dev(a, s[0], s[1])
+                                  for a, s in zip(args, spec)), st)
+    if rc != DORA_OK:
+        raise DoraError(name, rc)
 
 
 def dora_status_string(code: int) -> str:
@@ -162,8 +219,9 @@ def _dev(t: torch.Tensor, name: str, dtype=None) -> int:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:  # the current device's current stream
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if torch.cuda.is_initialized() else \
+            torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -215,11 +273,8 @@ def _select_pack_args(scores, keep, tokens, cu_in, N, idx_out, cu_out, packed_ou
         raise ValueError("packed_out must match the tokens' dtype and C")
     if int(idx_out.numel()) < cap_rows or int(packed_out.shape[0]) < cap_rows:
         raise ValueError("outputs smaller than cap_rows")
-    args = [_dev(scores, "scores", torch.float32), _dev(keep, "keep", torch.int32),
-            _dev(tokens, "tokens"), None if cu_in is None else _dev(cu_in, "cu_in", torch.int32),
-            total_in, B, int(N), C, _dtype_code(tokens),
-            _dev(idx_out, "idx_out", torch.int32), _dev(cu_out, "cu_out", torch.int32),
-            _dev(packed_out, "packed_out"), int(cap_rows)]
+    args = [scores, keep, tokens, cu_in, total_in, B, int(N), C, _dtype_code(tokens), idx_out, cu_out, packed_out,
+            int(cap_rows)]
     return args, (idx_out, cu_out, packed_out, dev_status)
 
 
@@ -240,11 +295,9 @@ def dora_select_pack(scores: torch.Tensor, keep: torch.Tensor, tokens: torch.Ten
     host synchronisation is needed): idx [cap], cu [B+1], packed [cap,C],
     dev_status [1].  Returns (idx_out, cu_out, packed_out, dev_status).
     """
-    lib = load_library()
     args, outs = _select_pack_args(scores, keep, tokens, cu_in, N, idx_out, cu_out, packed_out,
                                    cap_rows, dev_status)
-    rc = lib.dora_select_pack(*args, _dev(outs[3], "dev_status", torch.int32), _stream(stream))
-    _check("dora_select_pack", rc)
+    _call("dora_select_pack", stream, *args, outs[3])
     return outs
 
 
@@ -260,14 +313,10 @@ def dora_select_pack_plan(scores: torch.Tensor, keep: torch.Tensor, tokens: torc
     """dora_select_pack plus the attention plan of the packed output in `workspace`
     (for dora_varlen_attn_execute with cu_seqlens = cu_out, H heads, max_seqlen
     and total Q/K/V rows)."""
-    lib = load_library()
     args, outs = _select_pack_args(scores, keep, tokens, cu_in, N, idx_out, cu_out, packed_out,
                                    cap_rows, dev_status)
-    rc = lib.dora_select_pack_plan(*args, int(H), int(max_seqlen), int(total),
-                                   _dev(workspace, "workspace"),
-                                   workspace.numel() * workspace.element_size(),
-                                   _dev(outs[3], "dev_status", torch.int32), _stream(stream))
-    _check("dora_select_pack_plan", rc)
+    _call("dora_select_pack_plan", stream, *args, int(H), int(max_seqlen), int(total), workspace,
+          workspace.numel() * workspace.element_size(), outs[3])
     return outs
 
 
@@ -283,12 +332,10 @@ def dora_select_pack_residual(scores: torch.Tensor, keep: torch.Tensor, h: torch
     sum, each element rounded once to h's dtype.  a has h's shape and dtype."""
     if a.shape != h.shape or a.dtype != h.dtype:
         raise ValueError("a must have h's shape and dtype")
-    lib = load_library()
     args, outs = _select_pack_args(scores, keep, h, cu_in, N, idx_out, cu_out, packed_out,
                                    cap_rows, dev_status)
-    args.insert(3, _dev(a, "a", h.dtype))
-    rc = lib.dora_select_pack_residual(*args, _dev(outs[3], "dev_status", torch.int32), _stream(stream))
-    _check("dora_select_pack_residual", rc)
+    args.insert(3, a)
+    _call("dora_select_pack_residual", stream, *args, outs[3])
     return outs
 
 
@@ -310,11 +357,7 @@ def dora_actor_gate(p_gate: torch.Tensor, M: int, N: int, cu_in: Optional[torch.
     for t, name in ((on_rank, "on_rank"), (on_list, "on_list")):
         if t.numel() < B:
             raise ValueError(f"{name} needs {B} entries")
-    rc = load_library().dora_actor_gate(
-        _dev(p_gate, "p_gate", torch.float32), None if cu_in is None else _dev(cu_in, "cu_in", torch.int32),
-        B, int(N), int(M), _dev(on_rank, "on_rank", torch.int32), _dev(on_list, "on_list", torch.int32),
-        _dev(n_on, "n_on", torch.int32), _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_actor_gate", rc)
+    _call("dora_actor_gate", stream, p_gate, cu_in, B, int(N), int(M), on_rank, on_list, n_on, dev_status)
     return on_rank, on_list, n_on, dev_status
 
 
@@ -347,14 +390,8 @@ def dora_actor_decode(budget_logits: torch.Tensor, on_rank: torch.Tensor, N: int
             raise ValueError("cu_in must be [B+1]")
         total_in = int(removal_scores.shape[0]) if removal_scores is not None else 0
     dev_status = new_status(dev) if dev_status is None else dev_status
-    rc = load_library().dora_actor_decode(
-        _dev(budget_logits, "budget_logits", torch.float32) if rows > 0 else None, rows, M,
-        None if removal_scores is None else _dev(removal_scores, "removal_scores", torch.float32),
-        None if cu_in is None else _dev(cu_in, "cu_in", torch.int32), total_in, B, int(N),
-        _dev(on_rank, "on_rank", torch.int32), _dev(keep_out, "keep_out", torch.int32),
-        None if scores_out is None else _dev(scores_out, "scores_out", torch.float32),
-        _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_actor_decode", rc)
+    _call("dora_actor_decode", stream, budget_logits if rows > 0 else None, rows, M, removal_scores, cu_in, total_in,
+          B, int(N), on_rank, keep_out, scores_out, dev_status)
     return keep_out, scores_out, dev_status
 
 
@@ -390,13 +427,8 @@ def dora_pl_sample(scores: torch.Tensor, gumbel: torch.Tensor, k: torch.Tensor,
     dev_status = new_status(dev) if dev_status is None else dev_status
     if order_out.numel() < cap:
         raise ValueError("order_out smaller than cap")
-    rc = load_library().dora_pl_sample(
-        _dev(scores, "scores", torch.float32), _dev(gumbel, "gumbel", torch.float32), _dev(k, "k", torch.int32),
-        None if cu_in is None else _dev(cu_in, "cu_in", torch.int32), total_in, B, N,
-        _dev(order_out, "order_out", torch.int32), _dev(cu_order_out, "cu_order_out", torch.int32),
-        _dev(logprob_out, "logprob_out", torch.float32), int(cap), _dev(dev_status, "dev_status", torch.int32),
-        _stream(stream))
-    _check("dora_pl_sample", rc)
+    _call("dora_pl_sample", stream, scores, gumbel, k, cu_in, total_in, B, N, order_out, cu_order_out, logprob_out,
+          int(cap), dev_status)
     return order_out, cu_order_out, logprob_out, dev_status
 
 
@@ -411,12 +443,7 @@ def dora_pl_logprob(scores: torch.Tensor, order: torch.Tensor, cu_order: torch.T
     dev = scores.device
     logprob_out = torch.empty(B, dtype=torch.float32, device=dev) if logprob_out is None else logprob_out
     dev_status = new_status(dev) if dev_status is None else dev_status
-    rc = load_library().dora_pl_logprob(
-        _dev(scores, "scores", torch.float32), _dev(order, "order", torch.int32),
-        _dev(cu_order, "cu_order", torch.int32), None if cu_in is None else _dev(cu_in, "cu_in", torch.int32),
-        total_in, B, N, _dev(logprob_out, "logprob_out", torch.float32),
-        _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_pl_logprob", rc)
+    _call("dora_pl_logprob", stream, scores, order, cu_order, cu_in, total_in, B, N, logprob_out, dev_status)
     return logprob_out, dev_status
 
 
@@ -451,13 +478,9 @@ def dora_lc1_readout(x: torch.Tensor, cu_seqlens: torch.Tensor, gamma: torch.Ten
         raise ValueError("out must be [B, 2C]")
     if not single and workspace is None:
         workspace = new_lc1_workspace(B, C, x.device)
-    ws, ws_bytes = (None, 0) if single else (_dev(workspace, "workspace"), workspace.numel() * workspace.element_size())
-    rc = load_library().dora_lc1_readout(
-        _dev(x, "x"), _dev(cu_seqlens, "cu_seqlens", torch.int32), total, B, C, _dtype_code(x),
-        _dev(gamma, "gamma", torch.float32), _dev(beta, "beta", torch.float32), float(eps),
-        _dev(out, "out", torch.float32), ws, ws_bytes, _dev(dev_status, "dev_status", torch.int32),
-        _stream(stream))
-    _check("dora_lc1_readout", rc)
+    ws, ws_bytes = (None, 0) if single else (workspace, workspace.numel() * workspace.element_size())
+    _call("dora_lc1_readout", stream, x, cu_seqlens, total, B, C, _dtype_code(x), gamma, beta, float(eps), out, ws,
+          ws_bytes, dev_status)
     return out, dev_status
 
 
@@ -477,10 +500,7 @@ def dora_trajectory_flops(tokens: torch.Tensor, d: int, N0: int, patch: int, M: 
     flops_out = torch.empty(B, dtype=torch.int64, device=dev) if flops_out is None else flops_out
     total_out = torch.empty(1, dtype=torch.int64, device=dev) if total_out is None else total_out
     dev_status = new_status(dev) if dev_status is None else dev_status
-    rc = load_library().dora_trajectory_flops(
-        _dev(tokens, "tokens", torch.int32), B, ctypes.byref(cfg), _dev(flops_out, "flops_out", torch.int64),
-        _dev(total_out, "total_out", torch.int64), _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_trajectory_flops", rc)
+    _call("dora_trajectory_flops", stream, tokens, B, ctypes.addressof(cfg), flops_out, total_out, dev_status)
     return flops_out, total_out, dev_status
 
 
@@ -497,13 +517,9 @@ def new_workspace(B: int, H: int, max_seqlen: int, device=None) -> torch.Tensor:
 
 def dora_varlen_attn_plan(cu_seqlens: torch.Tensor, H: int, max_seqlen: int, total: int,
                           workspace: torch.Tensor, dev_status: torch.Tensor, stream=None) -> None:
-    lib = load_library()
     B = int(cu_seqlens.shape[0]) - 1
-    rc = lib.dora_varlen_attn_plan(_dev(cu_seqlens, "cu_seqlens", torch.int32), B, int(H),
-                                   int(max_seqlen), int(total), _dev(workspace, "workspace"),
-                                   workspace.numel() * workspace.element_size(),
-                                   _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_varlen_attn_plan", rc)
+    _call("dora_varlen_attn_plan", stream, cu_seqlens, B, int(H), int(max_seqlen), int(total), workspace,
+          workspace.numel() * workspace.element_size(), dev_status)
 
 
 def _attn_args(q, k, v, cu_seqlens, out):
@@ -523,17 +539,12 @@ def dora_varlen_attn_execute(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
                              cu_seqlens: torch.Tensor, max_seqlen: int, workspace: torch.Tensor,
                              out: Optional[torch.Tensor] = None, softmax_scale: float = 0.0,
                              dev_status: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
-    lib = load_library()
     total, H, D, out = _attn_args(q, k, v, cu_seqlens, out)
     if dev_status is None:
         dev_status = new_status(q.device)
     B = int(cu_seqlens.shape[0]) - 1
-    rc = lib.dora_varlen_attn_execute(
-        _dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(cu_seqlens, "cu_seqlens", torch.int32),
-        B, H, D, int(max_seqlen), total, float(softmax_scale), _dtype_code(q), _dev(out, "out"),
-        _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(),
-        _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_varlen_attn_execute", rc)
+    _call("dora_varlen_attn_execute", stream, q, k, v, cu_seqlens, B, H, D, int(max_seqlen), total, float(softmax_scale),
+          _dtype_code(q), out, workspace, workspace.numel() * workspace.element_size(), dev_status)
     return out
 
 
@@ -542,19 +553,14 @@ def dora_varlen_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqle
                      workspace: Optional[torch.Tensor] = None, softmax_scale: float = 0.0,
                      dev_status: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """softmax(scale * Q K^T) V inside each packed sequence; q/k/v/out [total, H, 64]."""
-    lib = load_library()
     total, H, D, out = _attn_args(q, k, v, cu_seqlens, out)
     B = int(cu_seqlens.shape[0]) - 1
     if workspace is None:
         workspace = new_workspace(B, H, max_seqlen, q.device)
     if dev_status is None:
         dev_status = new_status(q.device)
-    rc = lib.dora_varlen_attn(
-        _dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(cu_seqlens, "cu_seqlens", torch.int32),
-        B, H, D, int(max_seqlen), total, float(softmax_scale), _dtype_code(q), _dev(out, "out"),
-        _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(),
-        _dev(dev_status, "dev_status", torch.int32), _stream(stream))
-    _check("dora_varlen_attn", rc)
+    _call("dora_varlen_attn", stream, q, k, v, cu_seqlens, B, H, D, int(max_seqlen), total, float(softmax_scale),
+          _dtype_code(q), out, workspace, workspace.numel() * workspace.element_size(), dev_status)
     return out
 
 

@@ -17,6 +17,8 @@ LIB = os.path.join(PKG, "libdora.so")
 CALIB_LIB = os.path.join(PKG, "libdora_calibrate.so")
 CALIB_SOURCES = ["calibrate.hip"]
 SOURCES = ["select_pack.hip", "varlen_attn.hip", "actor_decode.hip", "pl_sample.hip", "lc1_readout.hip", "flops.hip"]
+# Native marshalling of the Python binding (host code only).
+HOST_LIB = os.path.join(PKG, "_host_call.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -50,7 +52,29 @@ def hipcc() -> str:
 def build(verbose: bool = False) -> str:
     _build_one(SOURCES, LIB, verbose)
     _build_one(CALIB_SOURCES, CALIB_LIB, verbose)
+    _build_host(verbose)
     return LIB
+
+
+def _build_host(verbose: bool) -> None:
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    tmp = HOST_LIB + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "host_call.cpp"),
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10",
+           "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("host build failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, HOST_LIB)
 
 
 def _build_one(sources, lib: str, verbose: bool) -> None:
