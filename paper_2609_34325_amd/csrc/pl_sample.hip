@@ -9,7 +9,7 @@
 // One workgroup per image.  Sampling: the keys s_j + g_j (g Gumbel noise,
 // passed in) of the visual tokens become 64-bit sort words (an
 // order-preserving image of the FP32 key above the position), are sorted in
-// LDS by a bitonic network, and the first k words give the draws in order.
+// registers by a bitonic network, and the first k words give the draws in order.
 // The same total order as select/pack on keep-scores -key (NaN drawn first,
 // equal keys by higher position), so the drawn set is exactly what select /
 // pack deletes with those keep-scores.  Log-probability: with m the largest
@@ -87,17 +87,15 @@ __device__ __forceinline__ long long block_sum_ll(long long v, long long* s_red)
   return t;
 }
 
-// Larger and smaller of a lane's 64-bit word and the word of lane ^ STRIDE
-// (STRIDE < 64, all lanes active), without a trip through the LDS crossbar
-// where the hardware offers a register path: DPP quad permutations (1, 2),
-// a DPP row rotation by 8 (XOR 8 within a row of 16 lanes), the swizzle's
-// XOR mode (4), and the row swaps of v_permlane16/32_swap (16, 32), which
-// hand each lane both words of its pair in some order -- all a min/max
-// needs.
+// A lane's 64-bit word and the word of lane ^ STRIDE (STRIDE < 64, all lanes
+// active), in some order, without a trip through the LDS crossbar where the
+// hardware offers a register path: DPP quad permutations (1, 2), a DPP row
+// rotation by 8 (XOR 8 within a row of 16 lanes), the swizzle's XOR mode (4),
+// and the row swaps of v_permlane16/32_swap (16, 32).
 template <int STRIDE>
-__device__ __forceinline__ void xor_minmax(unsigned long long x, unsigned long long& mx, unsigned long long& mn) {
+__device__ __forceinline__ void xor_pair(unsigned long long x, unsigned long long& a, unsigned long long& b) {
   const uint32_t lo = static_cast<uint32_t>(x), hi = static_cast<uint32_t>(x >> 32);
-  unsigned long long a = x, b;
+  a = x;
   if constexpr (STRIDE == 16 || STRIDE == 32) {
     const auto l2 = STRIDE == 16 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
                                  : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
@@ -123,30 +121,37 @@ __device__ __forceinline__ void xor_minmax(unsigned long long x, unsigned long l
     }
     b = (static_cast<unsigned long long>(ph) << 32) | pl;
   }
-  mx = a > b ? a : b;
-  mn = a < b ? a : b;
+}
+
+// The larger or the smaller of two words: one comparison and two selects.
+// (Forming both and selecting between them took twice the instructions.)
+__device__ __forceinline__ unsigned long long take(unsigned long long a, unsigned long long b, bool take_max) {
+  return (a > b) == take_max ? a : b;
 }
 
 // Descending bitonic sort of the P = E * kPLThreads sort words in LDS, E
 // words per thread in registers (element e = i * kPLThreads + thread id in
-// x[i]).  The same network as the LDS sort (pairs (lo, lo + stride),
-// descending where lo & size == 0): a step with stride < 64 pairs lanes of
-// one wave (xor_minmax, no barrier); stride 64 or 128 pairs waves through
+// x[i]).  The network's pairs are (lo, lo + stride), descending where
+// lo & size == 0: a step with stride < 64 pairs lanes of
+// one wave (xor_pair, no barrier); stride 64 or 128 pairs waves through
 // LDS between two barriers; stride >= kPLThreads pairs two registers of a
 // thread.  Called by every thread of the workgroup (uniformly), after the
 // words are in LDS and a barrier; the sorted words are back in LDS after a
-// final barrier.
+// final barrier.  Latency and VALU bound: per word and step two exchanges, a
+// 64-bit comparison and two selects.  The whole draw, 256 images (both minimum
+// and maximum formed per pair, and 2048 words sorted in LDS with a barrier
+// per step -> now): 197 tokens 5.8 -> 5.4 us, 577 12.0 -> 10.4, 2048 44 -> 18.7.
 __device__ __forceinline__ void cross_lane(unsigned long long& x, int stride, bool take_max) {
-  unsigned long long mx, mn;
+  unsigned long long a, b;
   switch (stride) {
-    case 1: xor_minmax<1>(x, mx, mn); break;
-    case 2: xor_minmax<2>(x, mx, mn); break;
-    case 4: xor_minmax<4>(x, mx, mn); break;
-    case 8: xor_minmax<8>(x, mx, mn); break;
-    case 16: xor_minmax<16>(x, mx, mn); break;
-    default: xor_minmax<32>(x, mx, mn); break;
+    case 1: xor_pair<1>(x, a, b); break;
+    case 2: xor_pair<2>(x, a, b); break;
+    case 4: xor_pair<4>(x, a, b); break;
+    case 8: xor_pair<8>(x, a, b); break;
+    case 16: xor_pair<16>(x, a, b); break;
+    default: xor_pair<32>(x, a, b); break;
   }
-  x = take_max ? mx : mn;
+  x = take(a, b, take_max);
 }
 
 template <int E>
@@ -167,9 +172,9 @@ __device__ void block_sort(unsigned long long* words) {
           if (i & rs) continue;
           const bool desc = ((i * kPLThreads + t) & size) == 0;
           const unsigned long long a = x[i], b = x[i | rs];
-          const unsigned long long mx = a > b ? a : b, mn = a < b ? a : b;
-          x[i] = desc ? mx : mn;
-          x[i | rs] = desc ? mn : mx;
+          const bool keep = (a > b) == desc;
+          x[i] = keep ? a : b;
+          x[i | rs] = keep ? b : a;
         }
       } else if (stride >= 64) {
         __syncthreads();  // every read of the previous exchange is done
@@ -181,7 +186,7 @@ __device__ void block_sort(unsigned long long* words) {
           const int e = i * kPLThreads + t;
           const unsigned long long y = words[e ^ stride];
           const bool take_max = ((e & stride) == 0) == ((e & size) == 0);  // lo of a descending pair, or hi of an ascending one
-          x[i] = take_max ? (x[i] > y ? x[i] : y) : (x[i] < y ? x[i] : y);
+          x[i] = take(x[i], y, take_max);
         }
       } else {
 #pragma unroll
@@ -293,31 +298,11 @@ __global__ __launch_bounds__(kPLThreads) void pl_kernel(PLParams p) {
 
   if constexpr (SAMPLE) {
     if (ok) {
-      // Bitonic sort, descending (earliest draw first): in registers, P / 256
-      // words per thread, up to 1024 words; wider rows in LDS, a barrier
-      // per step.
-      if (P == kPLThreads) {
-        block_sort<1>(s_word);
-      } else if (P == 2 * kPLThreads) {
-        block_sort<2>(s_word);
-      } else if (P == 4 * kPLThreads) {
-        block_sort<4>(s_word);
-      } else {
-        for (int size = 2; size <= P; size <<= 1) {
-          for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < P / 2; i += kPLThreads) {
-              const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-              const bool desc = (lo & size) == 0;
-              const unsigned long long x = s_word[lo], y = s_word[hi];
-              if ((x < y) == desc) {
-                s_word[lo] = y;
-                s_word[hi] = x;
-              }
-            }
-            __syncthreads();
-          }
-        }
-      }
+      // Bitonic sort, descending (earliest draw first), P / 256 words per thread.
+      if (P == kPLThreads) block_sort<1>(s_word);
+      else if (P == 2 * kPLThreads) block_sort<2>(s_word);
+      else if (P == 4 * kPLThreads) block_sort<4>(s_word);
+      else block_sort<8>(s_word);
       for (int u = tid; u < P; u += kPLThreads) {
         const int pos = static_cast<int>(s_word[u] & 0xFFFFFFFFu);  // 0 for padding
         if (u < kb) {

@@ -212,3 +212,16 @@ def test_capacity_overflow(gpu):
     assert torch.all(order[300:] == -7).item()
     o_o, c_o, _, _ = oracle.pl_sample(s, g, k)
     assert np.array_equal(order[:300].cpu().numpy(), o_o[:300]) and np.array_equal(c.cpu().numpy(), c_o)
+
+
+@pytest.mark.parametrize("N", [256, 258, 513, 514, 1025, 1026, 1300, 2047])
+@pytest.mark.parametrize("ties", [False, True])
+def test_sort_width_edges(gpu, N, ties):
+    """Around the widths of the register sort (256, 512, 1024, 2048 words), with
+    every key distinct and with few distinct keys, all tokens drawn or none left out."""
+    rng = np.random.default_rng(N + ties)
+    s = rng.standard_normal((3, N)).astype(np.float32)
+    g = rng.gumbel(size=(3, N)).astype(np.float32)
+    if ties:
+        s, g = np.round(s).astype(np.float32), np.round(g).astype(np.float32)
+    check(gpu, s, g, np.array([N - 1, N // 2, 1]))
