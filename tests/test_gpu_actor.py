@@ -162,3 +162,25 @@ def test_chain_on_device_matches_the_oracle_chain(gpu):
     want = oracle.varlen_attn(q, k, v, cu_o, "bf16")
     assert_attn_close(got, want, "bf16", "chain")
     print(f"[actor] chain: {n_o} of {w.B} gates open, sum keep {tot}", flush=True)
+
+
+@pytest.mark.parametrize("M", [1, 2, 16, 17, 63, 64, 65, 128, 129])
+def test_argmax_lane_edges(gpu, M):
+    """The budget argmax around its 16-lane rows and 64-lane waves: the winner in
+    every place, ties, signed zeros, rows of -inf and NaN in the last place."""
+    N = 2 * M + 5
+    logits = np.full((2 * M + 4, M), -3.0, np.float32)
+    logits[np.arange(M), np.arange(M)] = 2.0                 # one winner in each place
+    logits[np.arange(M, 2 * M), np.arange(M)] = np.nan       # NaN above every number
+    logits[2 * M] = -np.inf
+    logits[2 * M + 1] = 0.0
+    logits[2 * M + 1, ::2] = -0.0                            # -0 ties with +0: the first wins
+    logits[2 * M + 2, M - 1] = np.inf
+    logits[2 * M + 3] = -0.0
+    logits[2 * M + 3, M - 1] = 0.0
+    B = len(logits)
+    n, rank = np.full(B, N, np.int32), np.arange(B, dtype=np.int32)
+    keep, _, st = gpu.dora_actor_decode(to_dev(logits), to_dev(rank), N)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    assert np.array_equal(keep.cpu().numpy(), oracle.actor_budget(logits, n, rank))
