@@ -1,7 +1,7 @@
 // Native argument marshalling for the Python binding: call(index, address, args)
 // checks the tensors of one libdora entry point (plain tensors, on the GPU,
-// contiguous, the required type) and calls it at that address, with the GIL
-// held (every entry point only enqueues).  Anything else -- another object, a tensor subclass, an
+// contiguous, the required type) and calls it at that address, without the
+// GIL.  Anything else -- another object, a tensor subclass, an
 // active torch function mode, an argument that fails a check -- returns
 // NotImplemented, and the binding marshals the call through ctypes, which
 // raises the errors.  ctypes and the checks in Python cost about 5 us of a
@@ -159,7 +159,12 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         Py_RETURN_NOTIMPLEMENTED;
       }
     }
-    return PyLong_FromLong(entry.call(fn, a));
+    // A launch can wait for room in its queue: let other threads run, as ctypes does.
+    int rc = 0;
+    Py_BEGIN_ALLOW_THREADS
+    rc = entry.call(fn, a);
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(rc);
   } catch (...) {
     Py_RETURN_NOTIMPLEMENTED;
   }
