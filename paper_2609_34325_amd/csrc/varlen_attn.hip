@@ -33,6 +33,7 @@
 // the S^T output registers directly as its B operand (the key order inside a
 // 32-key step is permuted the same way on both operands).  The softmax
 // denominators come from the matrix unit as well: a block of ones times P^T.
+#include <float.h>
 #include <limits.h>
 #include <math.h>
 
@@ -887,6 +888,10 @@ struct F32State {
   floatx4 o[4];  // O^T, times kVScale
   float m, l;    // running max (raw units), this lane's share of the denominator
 };
+// The running max starts at the lowest finite value, not at -inf: keys of score
+// -inf before the first finite one then have weight exp2(-inf - m) = 0 and not
+// NaN.  (What it scales on the first finite score is zero.)
+constexpr float kMaxStart = -FLT_MAX;
 
 // One 64-key block (32 keys when HALF: the keys past kvalid are masked) of the
 // staged planes against the wave's 16 queries.
@@ -998,7 +1003,7 @@ __device__ __forceinline__ void f32_tile_direct(const AttnParams& p, long long s
   floatx4 o[4];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) o[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kMaxStart, l_run = 0.f;
 #pragma unroll 1
   for (int kb0 = 0; kb0 < len; kb0 += 16) {
     floatx4 s = {0.f, 0.f, 0.f, 0.f};
@@ -1187,7 +1192,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(AttnParams p) {
       }
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) st.o[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
-      st.m = -INFINITY;
+      st.m = kMaxStart;
       st.l = 0.f;
     }
     // The next stage's loads: the rest of this ticket's keys, or the next one's.
@@ -1260,7 +1265,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(AttnParams p) {
       float l = st.l + __shfl_xor(st.l, 16, 64);
       l += __shfl_xor(l, 32, 64);
       const float inv = 1.0f / (l * kVScale);
-      float bad = l * 0.0f;  // NaN when something is not finite
+      float bad = l * inv * 0.0f;  // NaN when something is not finite, or no key has weight
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
 #pragma unroll

@@ -91,3 +91,27 @@ def test_values_past_the_split(gpu, n, B):
         v = v0 * np.float32(scale)
         got, cu = run(gpu, q0, k0, v, lens)
         close(got / scale, oracle.varlen_attn(q0, k0, v0, cu, "f32"), scale)
+
+
+@pytest.mark.parametrize("B", [1, 64])                      # split and whole items
+@pytest.mark.parametrize("how", ["infinite", "overflow"])   # an infinite key, or finite factors whose product is
+@pytest.mark.parametrize("lead", [1, 15, 16, 17, 31, 32, 33, 63, 64, 96, 130, 209])
+def test_leading_keys_of_score_minus_infinity(gpu, lead, how, B):
+    """The first `lead` keys of a sequence score -inf: weight 0, the sequence without
+    them.  A sequence whose every score is -inf is NaN, as softmax gives."""
+    H, n = 2, 210
+    lens = [n] * B
+    rng = np.random.default_rng(lead)
+    q, k, v = workloads.random_qkv(rng, lens, H, "f32")
+    row0 = (B - 1) * n
+    k[row0:row0 + n, 0, 0] = 0.0
+    q[row0:row0 + n, 0, 0], k[row0:row0 + lead, 0, 0] = (1.0, -np.inf) if how == "infinite" else (2.0 ** 100, -2.0 ** 100)
+    got, _ = run(gpu, q, k, v, lens)
+    qs = q[row0:row0 + n].copy()
+    qs[:, 0, 0] = 0.0                          # times zero for the keys that stay
+    want = oracle.varlen_attn(np.ascontiguousarray(qs[lead:]), np.ascontiguousarray(k[row0 + lead:row0 + n]),
+                              np.ascontiguousarray(v[row0 + lead:row0 + n]), cu_of([n - lead]), "f32")
+    close(got[row0 + lead:row0 + n, 0], want[:, 0], (lead, how))
+    k[row0:row0 + n, 0, 0] = k[row0, 0, 0]
+    got, _ = run(gpu, q, k, v, lens)
+    assert np.all(np.isnan(got[row0:row0 + n, 0])) and np.all(np.isfinite(got[row0:row0 + n, 1]))
