@@ -816,10 +816,13 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16_kernel(AttnParams p) {
 // instructions straight from memory (f32_tile_direct): the split of an
 // infinity, or of a value that rounds to one, is not a number, so everything
 // that the split cannot represent ends there, and infinities and NaNs come
-// out as fp32 arithmetic gives them.  V is scaled by 2^32 before its split so
-// that its third term stays representable down to the smallest normal numbers.
-// (For Q and K a term lost at 2^-133 moves a score by nothing that fp32 could
-// show; weights below 2^-126 are zero in fp32 as well.)
+// out as fp32 arithmetic gives them.  The terms hold all bits while the last
+// bit of x is at least the smallest bf16 value, 2^-133 (the matrix instruction
+// takes subnormals), so while |x| >= 2^-110.  V and the weights are therefore
+// scaled by 2^16 before their splits, which covers every normal number (the
+// weights' scale leaves with the denominator's, V's at the end); a Q or K value
+// below 2^-110 other than zero sends its tiles to f32_tile_direct too: against
+// a large factor its lost bits can move a score.
 //
 // Work: the items and the queue of the bf16 kernel, a 16-query tile per wave.
 // K/V pass through registers, where they are split, into one of two LDS
@@ -840,7 +843,16 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16_kernel(AttnParams p) {
 // Largest error against 64 bits at 136 to 4000 tokens, relative in the
 // 2-norm: 3.4e-7 .. 9.2e-7 -> 1.3e-7 .. 2.1e-7.
 // ---------------------------------------------------------------------------
-constexpr float kVScale = 4294967296.0f;  // 2^32
+constexpr float kTermScale = 65536.0f;  // 2^16
+
+// Magnitudes as words that order like them, zero above all: bits << 1, less one.
+// The smallest of x's and those seen before.
+__device__ __forceinline__ uint32_t smallest(uint32_t seen, const float4& x) {
+  const uint32_t a = (__float_as_uint(x.x) << 1) - 1u, b = (__float_as_uint(x.y) << 1) - 1u;
+  const uint32_t c = (__float_as_uint(x.z) << 1) - 1u, d = (__float_as_uint(x.w) << 1) - 1u;
+  return min(min(min(min(seen, a), b), c), d);
+}
+constexpr uint32_t kWhole = ((127u - 110u) << 24) - 1u;  // word of 2^-110
 
 // The three bf16 terms of four values, two values per conversion.  (The empty
 // asm keeps a converted pair whole: left alone the compiler converts each
@@ -885,8 +897,8 @@ __device__ __forceinline__ floatx4 mfma_large(const bf16x8 (&a)[3], const bf16x8
 }
 
 struct F32State {
-  floatx4 o[4];  // O^T, times kVScale
-  float m, l;    // running max (raw units), this lane's share of the denominator
+  floatx4 o[4];  // O^T, times kTermScale twice
+  float m, l;    // running max (raw units), this lane's share of the denominator, times kTermScale
 };
 // The running max starts at the lowest finite value, not at -inf: keys of score
 // -inf before the first finite one then have weight exp2(-inf - m) = 0 and not
@@ -964,8 +976,8 @@ __device__ __forceinline__ void f32_block(const char* Ks, const char* Vs, LdsOff
     float x0[4], x1[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      x0[i] = __builtin_amdgcn_exp2f((s[2 * ks][i] - m_new) * scale_log2);
-      x1[i] = __builtin_amdgcn_exp2f((s[2 * ks + 1][i] - m_new) * scale_log2);
+      x0[i] = __builtin_amdgcn_exp2f((s[2 * ks][i] - m_new) * scale_log2) * kTermScale;
+      x1[i] = __builtin_amdgcn_exp2f((s[2 * ks + 1][i] - m_new) * scale_log2) * kTermScale;
       rs += x0[i] + x1[i];
     }
     split3(x0, t0);
@@ -1133,11 +1145,18 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(AttnParams p) {
       vn[u] = *reinterpret_cast<const float4*>(Vh + off);
     }
   };
+  // A key (below, a query) with a value too small for three terms becomes NaN,
+  // which takes the tiles that meet it to f32_tile_direct.  A lane's first staged
+  // row stands for both: where the second is a key, the first is one.
   auto store = [&](char* buf) {
+    uint32_t least = ~0u;
+#pragma unroll
+    for (int u = 0; u < kF32U; ++u) least = smallest(least, kn[u]);
+    if (least < kWhole) kn[0].x = __builtin_nanf("");
 #pragma unroll
     for (int u = 0; u < kF32U; ++u) {
       const float xk[4] = {kn[u].x, kn[u].y, kn[u].z, kn[u].w};
-      const float xv[4] = {vn[u].x * kVScale, vn[u].y * kVScale, vn[u].z * kVScale, vn[u].w * kVScale};
+      const float xv[4] = {vn[u].x * kTermScale, vn[u].y * kTermScale, vn[u].z * kTermScale, vn[u].w * kTermScale};
       u32x2 tk[3], tv[3];
       split3(xk, tk);
       split3(xv, tv);
@@ -1186,6 +1205,10 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(AttnParams p) {
     const int q0 = cur.qbeg + tile * 16;
     const bool active = len > 0 && q0 < cur.qend;
     if (sb == 0) {
+      uint32_t least = ~0u;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) least = smallest(least, qn[i]);
+      if (least < kWhole) qn[0].x = __builtin_nanf("");
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         const float x0[4] = {qn[2 * ks].x, qn[2 * ks].y, qn[2 * ks].z, qn[2 * ks].w};
@@ -1270,7 +1293,7 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(AttnParams p) {
     if (!more_keys && active && group == 0) {
       float l = st.l + __shfl_xor(st.l, 16, 64);
       l += __shfl_xor(l, 32, 64);
-      const float inv = 1.0f / (l * kVScale);
+      const float inv = 1.0f / (l * kTermScale);
       float bad = l * inv * 0.0f;  // NaN when something is not finite, or no key has weight
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)

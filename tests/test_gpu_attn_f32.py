@@ -115,3 +115,40 @@ def test_leading_keys_of_score_minus_infinity(gpu, lead, how, B):
     k[row0:row0 + n, 0, 0] = k[row0, 0, 0]
     got, _ = run(gpu, q, k, v, lens)
     assert np.all(np.isnan(got[row0:row0 + n, 0])) and np.all(np.isfinite(got[row0:row0 + n, 1]))
+
+
+@pytest.mark.parametrize("B", [1, 64])                # split and whole items
+@pytest.mark.parametrize("e", [100, 109, 110, 111, 114, 118, 120])
+@pytest.mark.parametrize("small", ["q", "k"])
+def test_small_factors_of_large_ones(gpu, small, e, B):
+    """Q near 2^-e against K near 2^e and the other way round: ordinary scores, of
+    which no bit of the small factor may be missing.  One sequence of the batch."""
+    H, n = 2, 210
+    lens = [n] * B
+    q, k, v = workloads.random_qkv(np.random.default_rng(e), lens, H, "f32")
+    s = slice((B - 1) * n, B * n)
+    for t in (q, k):                                  # at least 2^-5: normal numbers after the scaling
+        t[s] = np.copysign(np.maximum(np.abs(t[s]), 2.0 ** -5), t[s])
+    q[s] *= np.float32(2.0 ** (-e if small == "q" else e))
+    k[s] *= np.float32(2.0 ** (e if small == "q" else -e))
+    got, cu = run(gpu, q, k, v, lens)
+    close(got, oracle.varlen_attn(q, k, v, cu, "f32"), (small, e))
+
+
+@pytest.mark.parametrize("B", [1, 64])
+@pytest.mark.parametrize("x", [100, 110, 118, 122, 125])
+def test_small_weights_of_large_values(gpu, x, B):
+    """One key of weight 1 and value 0, all others of weight near 2^-x and positive
+    values: what the small weights say is the whole result."""
+    H, n = 2, 210
+    lens = [n] * B
+    q, k, v = workloads.random_qkv(np.random.default_rng(x), lens, H, "f32")
+    q[:, :, 0], k[:, :, 0] = 8.0, -np.float32(x * np.log(2.0))
+    q[:, :, 1:] *= np.float32(0.05)
+    k[n // 2::n, :, 0], k[n // 2::n, :, 1:] = 0.0, 0.0
+    v = (np.abs(v) + np.float32(0.1)) * np.float32(2.0 ** 80)
+    v[n // 2::n] = 0.0
+    got, cu = run(gpu, q, k, v, lens)
+    want = oracle.varlen_attn(q, k, v, cu, "f32")
+    # exp2's argument is up to 126 and carries about 6 roundings of 6e-8: 126 ln 2 * 6 * 6e-8 = 3.1e-5 of a weight
+    assert np.abs(got / want - 1).max() <= 4e-5
