@@ -1005,37 +1005,66 @@ __device__ __forceinline__ void f32_block(const char* Ks, const char* Vs, LdsOff
 }
 
 // The wave's 16 queries q0 .. (below qend) against all keys of the sequence,
-// with v_mfma_f32_16x16x4_f32 and operands read from memory, O written.  Slow;
-// only for tiles whose split result is not finite.
+// with v_mfma_f32_16x16x4_f32 and operands read from memory, O written.  Only
+// for tiles whose split result is not finite.
 //
 // MFMA 16x16x4 f32 operand layout (lane l, g = l / 16, c = l % 16):
 //   A[16 x 4]: lane holds row c, k = g;  B[4 x 16]: lane holds column c, k = g
 //   D[16 x 16]: lane holds column c, rows 4g .. 4g+3
+//
+// The dimensions are dealt so that a lane's operands are whole 16-byte pieces:
+// step 4 j + e of K Q^T takes dimension 16 g + 4 j + e, and row c of V^T's tile dt
+// is dimension 4 c + dt.  Bound by three memory round trips and 32 matrix
+// instructions of 32 cycles per 16 keys; more loads in flight would take registers
+// from the key loop of the kernel it is part of, which then spills.  Whole pass on
+// NaN inputs, one load at a time -> now (fp32 matrix instructions for every tile
+// from the start): 64 sequences of 136 tokens with 12 heads 320 -> 116 us (94), 64
+// of 577 4882 -> 1525 (838), one of 4096 with 3 heads 1851 -> 522 (190).
 __device__ __forceinline__ void f32_tile_direct(const AttnParams& p, long long seq0, int len, int h, int q0, int qend) {
-  const int lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // addresses are formed here, not ahead of the caller's key loop
+  const int c16 = lane & 15, g = lane >> 4;
   const long long row_elems = static_cast<long long>(p.H) * kD;
-  const float* Q = static_cast<const float*>(p.q) + seq0 * row_elems + h * kD;
-  const float* K = static_cast<const float*>(p.k) + seq0 * row_elems + h * kD;
-  const float* V = static_cast<const float*>(p.v) + seq0 * row_elems + h * kD;
-  const int qi = q0 + c16;
+  const uint32_t row_bytes = static_cast<uint32_t>(p.H) * kD * 4u;
+  const char* Kb = reinterpret_cast<const char*>(static_cast<const float*>(p.k) + seq0 * row_elems + h * kD);
+  const char* Vb = reinterpret_cast<const char*>(static_cast<const float*>(p.v) + seq0 * row_elems + h * kD);
+  floatx4 v[4];
+  const float* Q = static_cast<const float*>(p.q) + (seq0 + min(q0 + c16, qend - 1)) * row_elems + h * kD + 16 * g;
+  // Rows past the last key repeat it: their scores are masked, their V cleared.
+  auto load_v = [&](int left, floatx4 (&x)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      x[j] = *reinterpret_cast<const floatx4*>(Vb + static_cast<uint32_t>(min(4 * g + j, left - 1)) * row_bytes +
+                                               static_cast<uint32_t>(c16) * 16u);
+    Vb += 16 * static_cast<long long>(row_bytes);
+  };
   floatx4 o[4];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) o[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
   float m_run = kMaxStart, l_run = 0.f;
 #pragma unroll 1
-  for (int kb0 = 0; kb0 < len; kb0 += 16) {
+  for (int left = len; left > 0; left -= 16) {
     floatx4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int ks = 0; ks < 16; ++ks) {
-      const float a = kb0 + c16 < len ? K[(kb0 + c16) * row_elems + 4 * ks + g] : 0.f;
-      const float b = qi < qend ? Q[qi * row_elems + 4 * ks + g] : 0.f;
-      s = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, s, 0, 0, 0);
+    const char* kr = Kb + static_cast<uint32_t>(min(c16, left - 1)) * row_bytes + static_cast<uint32_t>(g) * 64u;
+#pragma unroll 2
+    for (int j = 0; j < 4; ++j) {
+      const floatx4 k = reinterpret_cast<const floatx4*>(kr)[j], q = reinterpret_cast<const floatx4*>(Q)[j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[e], q[e], s, 0, 0, 0);
     }
+    Kb += 16 * static_cast<long long>(row_bytes);
+    asm volatile("" ::: "memory");
+    load_v(left, v);
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      s[i] = kb0 + 4 * g + i < len ? s[i] : -INFINITY;
+      s[i] = 4 * g + i < left ? s[i] : -INFINITY;
       mx = fmaxf(mx, s[i]);
+    }
+    if (left < 16) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * g + i >= left) v[i] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
     const float m_new = fmaxf(m_run, row_group_max(mx));
     const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * p.scale_log2);
@@ -1049,24 +1078,21 @@ __device__ __forceinline__ void f32_tile_direct(const AttnParams& p, long long s
     l_run = l_run * alpha + rs;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
-    // MFMA k = g <-> key kb0 + 4g + i.
+    // MFMA k = g <-> key 4g + i of the block.
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const float a = kb0 + 4 * g + i < len ? V[(kb0 + 4 * g + i) * row_elems + dt * 16 + c16] : 0.f;
-        o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, s[i], o[dt], 0, 0, 0);
-      }
+      for (int dt = 0; dt < 4; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i][dt], s[i], o[dt], 0, 0, 0);
   }
   float l = l_run + __shfl_xor(l_run, 16, 64);
   l += __shfl_xor(l, 32, 64);
   const float inv = 1.0f / l;
-  if (qi < qend) {
-    float* dst = static_cast<float*>(p.out) + (seq0 + qi) * row_elems + h * kD + 4 * g;
+  if (q0 + c16 < qend) {
+    // o[dt][r]: dimension 4 (4g + r) + dt.
+    float* dst = static_cast<float*>(p.out) + (seq0 + q0 + c16) * row_elems + h * kD + 16 * g;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-      *reinterpret_cast<float4*>(dst + dt * 16) =
-          make_float4(o[dt][0] * inv, o[dt][1] * inv, o[dt][2] * inv, o[dt][3] * inv);
+    for (int r = 0; r < 4; ++r)
+      *reinterpret_cast<float4*>(dst + 4 * r) = make_float4(o[0][r] * inv, o[1][r] * inv, o[2][r] * inv, o[3][r] * inv);
   }
 }
 

@@ -152,3 +152,14 @@ def test_small_weights_of_large_values(gpu, x, B):
     want = oracle.varlen_attn(q, k, v, cu, "f32")
     # exp2's argument is up to 126 and carries about 6 roundings of 6e-8: 126 ln 2 * 6 * 6e-8 = 3.1e-5 of a weight
     assert np.abs(got / want - 1).max() <= 4e-5
+
+
+@pytest.mark.parametrize("H", [1, 12])
+def test_recomputed_tiles_edges(gpu, H):
+    """Every tile through the fp32 matrix instructions (V past the split's range)."""
+    rng = np.random.default_rng(H + 40)
+    groups = [LENS] if H > 1 else [LENS[i:i + 4] for i in range(0, len(LENS), 4)]
+    for lens in groups:
+        q, k, v = workloads.random_qkv(rng, lens, H, "f32")
+        got, cu = run(gpu, q, k, v * np.float32(2.0 ** 115), lens)
+        close(got / 2.0 ** 115, oracle.varlen_attn(q, k, v, cu, "f32"), lens)
