@@ -1287,6 +1287,9 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_f32_kernel(AttnParams p) {
       s_raw[par] = raw_next;
       s_part[par] = t_nn % kParts;
       t_nn = t_got + 3 * Gq;
+      // The ticket is waited for here, also before the last stage's exit, where
+      // it is not used: leave_queue counts on it.
+      asm volatile("" : "+v"(t_nn));
     }
     if (!more_keys && nx.len > 0) fetch_q(nx);
     if (have_next && (more_keys || nx.len > 0)) store(lds[1 - par]);

@@ -163,3 +163,33 @@ def test_recomputed_tiles_edges(gpu, H):
         q, k, v = workloads.random_qkv(rng, lens, H, "f32")
         got, cu = run(gpu, q, k, v * np.float32(2.0 ** 115), lens)
         close(got / 2.0 ** 115, oracle.varlen_attn(q, k, v, cu, "f32"), lens)
+
+
+# (sequences, heads): split items, and 3 or more whole items per workgroup (tickets from the counters)
+@pytest.mark.parametrize("B,H", [(2, 3), (64, 16)])
+def test_one_plan_many_executes(gpu, B, H):
+    """One plan for several layers, fp32 and bf16 in turn on one workspace: every
+    layer writes every row, and the queue's counters are zero after each."""
+    rng = np.random.default_rng(B)
+    lens = rng.integers(1, 400, size=B)
+    mx, total = int(lens.max()), int(lens.sum())
+    q, k, v = workloads.random_qkv(rng, lens, H, "f32")
+    cu = cu_of(lens)
+    want = oracle.varlen_attn(q, k, v, cu, "f32")
+    f32 = [to_dev(t) for t in (q, k, v)]
+    bf16 = [t.bfloat16() for t in f32]
+    ws, st, cu_d = gpu.new_workspace(B, H, mx), gpu.new_status(), to_dev(cu)
+    gpu.dora_varlen_attn_plan(cu_d, H, mx, total, ws, st)
+    first = {}
+    for layer in range(6):
+        x = bf16 if layer in (2, 3) else f32
+        out = torch.full_like(x[0], -777.0)
+        gpu.dora_varlen_attn_execute(*x, cu_d, mx, ws, out=out, dev_status=st)
+        torch.cuda.synchronize()
+        head = ws[:2048].view(torch.int32).cpu().numpy()
+        assert int(st.item()) == 0 and np.all(head[64:64 + 32 * 9:32] == 0)   # eight ticket counters, the exit counter
+        if x is f32:
+            close(out.cpu().numpy().astype(np.float64), want, layer)
+        else:  # inputs rounded to bf16: scores of up to 5 off by 2^-8, weights by 2 %, of values up to 4
+            assert np.abs(out.float().cpu().numpy() - want).max() <= 0.1
+        assert torch.equal(out, first.setdefault(x is f32, out))
