@@ -33,6 +33,7 @@
 #include <limits.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "attn_plan.h"
 #include "dora_internal.h"
@@ -46,8 +47,13 @@ constexpr int kDigitSelectSlots = 8;  // rows of more than 256 tokens select by 
 // operands in the residual variant).  Inputs rotating through more than the
 // last-level cache holds, 2 -> 8 loads at the split below: 8192 images of 197
 // rows of 1536 bytes 626 -> 602 us, 1024 images 81.1 -> 78.8, 256 images 25.1
-// -> 25.1; residual 1024 images 124 -> 120, 256 images 36.5 -> 34.7.
+// -> 25.1; residual 1024 images 124 -> 120, 256 images 36.5 -> 34.7.  Where no
+// more than two per lane are left, two: 8192 images of 30 rows of 128 bytes 30.0
+// -> 29.0.
 constexpr int kCopyLoads = 8;
+// Workgroups that share an image: one per 32 KB of its kept rows (pick_split).
+constexpr int kPieceVecs = 2048;
+constexpr int kOrderGroup = 32;
 // Up to this many images each workgroup sums keep[0..b) itself (at most 8 KB
 // of keep counts from the L2, cheaper than a second launch); above it one
 // workgroup scans the keep counts into cu_out first.
@@ -63,6 +69,7 @@ struct SelectPackParams {
   const int32_t* cu_in;
   int64_t total_in;
   int32_t B, N, row_vecs, split;
+  int32_t fill_split;  // workgroups per image that take part however few rows it keeps
   int32_t* idx_out;
   int32_t* cu_out;
   uint4* packed;
@@ -275,8 +282,22 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int b = block / p.split;
-  const int s = block - b * p.split;
+  // Workgroup (b, s).  Where an image's size has brought workgroups (pick_split),
+  // those of kOrderGroup images come piece by piece: with an image's pieces side
+  // by side, the ones that take no part would leave whole XCDs idle (1024 images
+  // of 577 tokens, 50 of them kept: 55 to 101 us, so 33).
+  int b = block, s = 0;
+  if (p.split == p.fill_split) {
+    if (p.split > 1) {
+      b = block / p.split;
+      s = block - b * p.split;
+    }
+  } else {
+    const int first = block / (kOrderGroup * p.split) * kOrderGroup, i = block - first * p.split;
+    const int images = min(kOrderGroup, p.B - first);
+    s = images == kOrderGroup ? i / kOrderGroup : i / images;
+    b = first + i - s * images;
+  }
 
   // Segment of image b in the input.
   long long off_in, n;
@@ -291,6 +312,15 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
     n = p.N;
   }
   const int kb = p.keep[b];
+  // Workgroups that take part: of those that the image's size has brought, one per
+  // kPieceVecs of the rows that are kept; the others would repeat the selection
+  // for a few rows each.
+  int split = p.split;
+  if (split > p.fill_split) {
+    const long long pieces = (static_cast<long long>(kb) * p.row_vecs + kPieceVecs / 2) / kPieceVecs;
+    split = static_cast<int>(min(max(pieces, static_cast<long long>(p.fill_split)), static_cast<long long>(split)));
+    if (s >= split) return;  // s > 0: the image's first workgroup always stays
+  }
   const long long cu_b = p.cu_ready ? static_cast<long long>(p.cu_out[b]) : 0;
   // Wave 0's score loads go out before the keep count is checked: they
   // depend on the segment only, so they overlap the keep count's load instead
@@ -421,7 +451,9 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
     if (img_ok) wide_select<kSel>(x, n, kb, lane, wave, s_hist, s_cnt, s_idx);  // img_ok: uniform in the workgroup
   }
   __syncthreads();
-  const long long off_out = p.cu_ready ? cu_b : s_part[1] + s_part[2] + s_part[3];
+  long long off_out = p.cu_ready ? cu_b : s_part[1] + s_part[2] + s_part[3];
+  off_out = static_cast<long long>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(off_out)))) |
+            static_cast<long long>(__builtin_amdgcn_readfirstlane(static_cast<int>(off_out >> 32))) << 32;
 
   if (plan_img && kb >= 1 && kb <= p.max_seqlen) {
     // Items (b, h, c) for head h and query chunk c, each in its slot of the
@@ -465,7 +497,7 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
   }
 
   // This workgroup's share of the kept rows.
-  const int rows_per = (kb + p.split - 1) / p.split;
+  const int rows_per = (kb + split - 1) / split;
   const int r0 = s * rows_per;
   const int r1 = min(kb, r0 + rows_per);
   if (r0 >= r1) return;
@@ -476,22 +508,27 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
   int row = tid / vpr;
   int vec = tid - row * vpr;
   // Stores go through a buffer resource based at this workgroup's first
-  // output row (offsets below 2^31: at most N rows of at most 1 MB); a row at
-  // or past cap_rows gets an offset past the resource and is dropped.
-  const __amdgpu_buffer_rsrc_t out = raw_buffer(p.packed + (off_out + r0) * vpr);
-  for (int base = tid; base < nvec; base += kThreads * kCopyUnroll) {
-    uint4 buf[kCopyUnroll], add[kCopyUnroll];
-    uint32_t dst[kCopyUnroll];
+  // output row (offsets below 2^31: at most N rows of at most 1 MB); rows outside
+  // [0, cap_rows) get an offset past the resource and are dropped.
+  const long long out0 = off_out + r0;
+  const __amdgpu_buffer_rsrc_t out = raw_buffer(p.packed + out0 * vpr);
+  const int lo = static_cast<int>(min(max(-out0, 0ll), static_cast<long long>(r1 - r0))) * vpr;
+  const int hi = static_cast<int>(min(max(p.cap_rows - out0, 0ll), static_cast<long long>(r1 - r0))) * vpr;
+  const uint32_t stored = static_cast<uint32_t>(max(hi - lo, 0));
+  const char* const src = reinterpret_cast<const char*>(p.tokens + off_in * vpr);
+  const char* const src2 = MODE == kCopy ? nullptr : reinterpret_cast<const char*>(p.addend + off_in * vpr);
+  int base = tid;
+  auto copy = [&](auto loads) {
+    constexpr int kLoads = decltype(loads)::value;
+    uint4 buf[kLoads], add[kLoads];
 #pragma unroll
-    for (int u = 0; u < kCopyUnroll; ++u) {
+    for (int u = 0; u < kLoads; ++u) {
       const bool in_range = base + u * kThreads < nvec;
-      const int pos = s_idx[in_range ? r0 + row : r0];
-      const long long src_row = off_in + min(max(pos, 0), static_cast<int>(n) - 1);  // always inside the segment
-      const long long out_row = off_out + r0 + row;
-      buf[u] = in_range ? p.tokens[src_row * vpr + vec] : make_uint4(0u, 0u, 0u, 0u);
-      if constexpr (MODE != kCopy) add[u] = in_range ? p.addend[src_row * vpr + vec] : make_uint4(0u, 0u, 0u, 0u);
-      dst[u] = (in_range && out_row >= 0 && out_row < p.cap_rows) ? static_cast<uint32_t>(row * vpr + vec) * 16u
-                                                                   : 0xFFFFFFF0u;
+      const int pos = min(max(s_idx[in_range ? r0 + row : r0], 0), static_cast<int>(n) - 1);  // always inside the segment
+      const uint32_t off = static_cast<uint32_t>(pos * vpr + vec) * 16u;  // below 2^31
+      buf[u] = in_range ? *reinterpret_cast<const uint4*>(src + off) : make_uint4(0u, 0u, 0u, 0u);
+      if constexpr (MODE != kCopy)
+        add[u] = in_range ? *reinterpret_cast<const uint4*>(src2 + off) : make_uint4(0u, 0u, 0u, 0u);
       row += step_rows;
       vec += step_vecs;
       if (vec >= vpr) {
@@ -499,9 +536,17 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
         ++row;
       }
     }
+    __builtin_amdgcn_sched_barrier(0);  // all loads before the first store
 #pragma unroll
-    for (int u = 0; u < kCopyUnroll; ++u) store_through(out, dst[u], combine<MODE>(buf[u], add[u]));
-  }
+    for (int u = 0; u < kLoads; ++u) {
+      const uint32_t e = static_cast<uint32_t>(base + u * kThreads);  // piece of the workgroup's rows
+      store_through(out, e - static_cast<uint32_t>(lo) < stored ? e * 16u : 0xFFFFFFF0u, combine<MODE>(buf[u], add[u]));
+    }
+    base += kThreads * kLoads;
+  };
+  // The last pieces two at a time where two are all.
+  while (nvec - (base - tid) > 2 * kThreads) copy(std::integral_constant<int, kCopyUnroll>{});
+  if (base - tid < nvec) copy(std::integral_constant<int, 2>{});
 }
 
 // One workgroup per (image, split) piece.  The plain variant copies rows; the
@@ -584,34 +629,44 @@ __global__ __launch_bounds__(kScanThreads) void keep_scan_kernel(const int32_t* 
 template <int SLOTS>
 hipError_t launch(const SelectPackParams& p, const PlanParams* plan, int mode, hipStream_t stream) {
   const dim3 grid(p.B * p.split), block(kThreads);
+  // Long copies by fewer workgroups at a time: LDS that none uses leaves room for
+  // seven per compute unit (five with the plan's) instead of eight.  8192 images
+  // of 303 KB 622 -> 612 us, of 76 KB 163 -> 155.  The kernels for longer rows hold
+  // 16 KB anyway, and lose by more (2048 packed images of 154 KB 61 -> 68).
+  const unsigned lds = p.split > p.fill_split && SLOTS < kDigitSelectSlots ? 21 << 10 : 0;
   if (plan != nullptr)
-    hipLaunchKernelGGL(select_pack_planning_kernel<SLOTS>, dim3(p.B * p.split + 1), block, 0, stream, p, *plan);
+    hipLaunchKernelGGL(select_pack_planning_kernel<SLOTS>, dim3(p.B * p.split + 1), block, lds, stream, p, *plan);
   else if (mode == kAddBf16)
-    hipLaunchKernelGGL((select_pack_residual_kernel<SLOTS, kAddBf16>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((select_pack_residual_kernel<SLOTS, kAddBf16>), grid, block, lds, stream, p);
   else if (mode == kAddF32)
-    hipLaunchKernelGGL((select_pack_residual_kernel<SLOTS, kAddF32>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((select_pack_residual_kernel<SLOTS, kAddF32>), grid, block, lds, stream, p);
   else
-    hipLaunchKernelGGL(select_pack_kernel<SLOTS>, grid, block, 0, stream, p);
+    hipLaunchKernelGGL(select_pack_kernel<SLOTS>, grid, block, lds, stream, p);
   return hipGetLastError();
 }
 
-// Workgroups per image: about 48 KB of the image's rows each, at most 8, so
-// that the selection of one workgroup runs under the copies of others and the
-// last round of workgroups is short; more where the batch alone would leave
-// the chip idle (about 4 workgroups per compute unit).  Cold inputs, 1 / 2 / 4
-// / 6 / 8 workgroups per image: 8192 images of 303 KB 675 / 659 / 642 / 602 /
-// 608 us, 1024 of 303 KB 92.6 / 87.4 / 81.1 / 78.8 / 78.2, 256 of 886 KB 72.7 /
-// 71.9 / 68.7 / 68.6 / 66.5, 8192 of 76 KB 171 / 157 / 180 / 250 / 323, 4096 of
-// 25 KB 33.5 / 41.2 / 65 (each workgroup repeats the selection).
-int pick_split(int B, int N, int64_t row_bytes) {
-  constexpr int64_t kPiece = 48 << 10;
-  const int by_bytes = static_cast<int>(std::min<int64_t>((N * row_bytes + kPiece / 2) / kPiece, 8));
-  int split = std::max((1024 + B - 1) / B, by_bytes);
-  const int max_split = N / 16 > 1 ? N / 16 : 1;  // at least ~16 rows per workgroup
-  if (split > max_split) split = max_split;
-  if (split < 1) split = 1;
-  while (static_cast<long long>(split) * B > INT_MAX) --split;
-  return split;
+// Workgroups per image: enough for the batch to fill the chip (about 4 per
+// compute unit: *fill_split), and one per 32 KB of kept rows, at most 8, so that
+// the selection of one workgroup runs under the copies of others and the last
+// round of workgroups is short.  More cost more than they give, since each
+// repeats the selection.  Cold inputs, 1 / 2 / 4 / 6 / 8 workgroups per image, half of the rows kept:
+// 8192 images of 303 KB 675 / 659 / 642 / 602 / 608 us, 1024 of 303 KB 92.6 /
+// 87.4 / 81.1 / 78.8 / 78.2, 256 of 886 KB 72.7 / 71.9 / 68.7 / 68.6 / 66.5, 8192 of
+// 76 KB 171 / 157 / 180 / 250 / 323, 4096 of 25 KB 33.5 / 41.2 / 65.  (24 KB: 8192 of
+// 303 KB 2 % faster, 256 of 303 KB 6 % slower.)  `rows`: what the
+// host knows of an image's kept rows: at most the output's capacity per image, the
+// input's tokens per image (packed; N is only a bound there) and N.  By N alone:
+// 2048 packed images of 10 tokens with N = 2048 129 us, so 25; 1024 images of
+// which 12 of 197 tokens stay 22.6, so 8.8 (14 where the capacity does not say it and
+// the kernel leaves the workgroups out).
+int pick_split(int B, int N, int64_t rows, int row_vecs, int* fill_split) {
+  const int64_t max_split = std::max(N / 16, 1);  // at least ~16 rows per workgroup
+  const int64_t fill = std::min<int64_t>((1024 + static_cast<int64_t>(B) - 1) / B, max_split);
+  int64_t split = std::max(fill, std::min({(rows * row_vecs + kPieceVecs / 2) / kPieceVecs, int64_t(8), max_split}));
+  // A launch holds fewer than 2^32 threads, the plan's workgroup among them.
+  while (split > 1 && (static_cast<int64_t>(B) * split + 1) * kThreads >= int64_t(1) << 32) --split;
+  *fill_split = static_cast<int>(std::min(fill, split));
+  return static_cast<int>(split);
 }
 
 // Checks the arguments of a select/pack call and fills `p` (no plan).
@@ -637,7 +692,9 @@ int prepare(const float* scores, const int32_t* keep, const void* tokens, const 
   p->B = B;
   p->N = N;
   p->row_vecs = static_cast<int32_t>(row_bytes / 16);
-  p->split = pick_split(B, N, row_bytes);
+  // Rows an image keeps, on average, as far as the host knows.
+  const int64_t in_rows = cu_in != nullptr ? std::min<int64_t>(N, (total_in + B - 1) / B) : N;
+  p->split = pick_split(B, N, std::min(in_rows, (cap_rows + B - 1) / B), p->row_vecs, &p->fill_split);
   p->idx_out = idx_out;
   p->cu_out = cu_out;
   p->packed = static_cast<uint4*>(packed_out);

@@ -255,3 +255,39 @@ def test_large_batch_errors_write_nothing_past_cap(gpu):
     idx_o, cu_o, packed_o, _ = oracle.select_pack(scores, keep, tokens)
     assert np.array_equal(idx, idx_o[:1000]) and np.array_equal(packed, packed_o[:1000])
     assert np.array_equal(cu, cu_o)
+
+
+# 1050 images: the last group of 32 is not whole.  A workgroup more from 16, 48, 80, .. kept rows (C = 512), from 43, 128, .. (192).
+@pytest.mark.parametrize("N,C,packed", [(300, 512, False), (197, 512, True), (40, 1536, False), (400, 192, True)])
+def test_workgroups_by_kept_rows(gpu, N, C, packed):
+    """More workgroups per image than the batch needs, of which those take part that
+    the kept rows ask for: from one row to all, around the places where one more does."""
+    B = 1050
+    rng = np.random.default_rng(N + C)
+    n = rng.integers(max(1, N - 40), N + 1, B).astype(np.int32) if packed else np.full(B, N, np.int32)
+    edges = np.array([1, 2, 15, 16, 17, 42, 43, 47, 48, 49, 79, 80, 81, 127, 128, 129, N])
+    keep = np.minimum(rng.choice(edges, B), n).astype(np.int32)
+    total = int(n.sum())
+    tokens = rng.integers(0, 2 ** 16, size=(total, C), dtype=np.uint16)
+    scores = rng.standard_normal(total).astype(np.float32)
+    if packed:
+        check_round(gpu, scores, keep, tokens, cu_in=np.concatenate([[0], np.cumsum(n)]).astype(np.int32), N=N)
+        cap = total // 3
+        idx_g, _, packed_g, st, canary = run_gpu(gpu, scores, keep, tokens, N=N, cap=cap, guard=64,
+                                                 cu_in=np.concatenate([[0], np.cumsum(n)]).astype(np.int32))
+        assert canary and (st == gpu.DORA_DEV_CAPACITY) == (int(keep.sum()) > cap)
+    else:
+        check_round(gpu, scores.reshape(B, N), keep, tokens.reshape(B, N, C))
+
+
+def test_short_images_under_a_large_bound(gpu):
+    """Packed input whose N is far above its images: 2.2 million images of one token
+    (by the bound alone the launch would not hold the workgroups)."""
+    B, C, N = 2_200_000, 96, 2048
+    tokens = torch.arange(B * C, device="cuda").remainder_(30011).to(torch.int16).view(torch.bfloat16).view(B, C)
+    one = torch.ones(B, dtype=torch.int32, device="cuda")
+    cu = torch.arange(B + 1, dtype=torch.int32, device="cuda")
+    idx, cu_out, packed, st = gpu.dora_select_pack(torch.zeros(B, device="cuda"), one, tokens, cu_in=cu, N=N, cap_rows=B)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0 and torch.equal(cu_out, cu) and not bool(idx.any())
+    assert torch.equal(packed.view(torch.int16), tokens.view(torch.int16))
