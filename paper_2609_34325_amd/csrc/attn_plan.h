@@ -5,10 +5,16 @@
 // Three passes: count the sequences by length (1024 bins), turn the counts
 // into positions of the longest-first order and into the item bases of each
 // class (sequences of equal chunk count), and give every sequence its position
-// (an LDS atomic on its bin) and with it its items' slots.  Nothing but the
-// bins and class tables lives in LDS (about 6 KB), so a workgroup that makes a
-// plan does not crowd out copying ones.  Latency bound: a few memory round
-// trips and, for many sequences, the item stores of one compute unit.
+// (an LDS atomic on its bin) and with it its items' slots.  Latency bound: a few
+// memory round trips and, for many sequences, the item stores of one compute
+// unit.
+//
+// ORDER (the plan kernel) sorts more sequences than the workgroup has threads
+// in LDS first, so that the lanes of a wave write neighbouring slots: 8192
+// sequences of 20 to 197 tokens with 12 heads 61 us by input order, 55 sorted (3
+// heads 19.7 and 14.6); up to 1024 sequences the extra pass costs more than it
+// gives.  Beside copying workgroups nothing but the bins and class tables is
+// held in LDS (about 6 KB), so that the plan's workgroup does not crowd them out.
 #pragma once
 
 #include "dora_internal.h"
@@ -44,7 +50,7 @@ inline PlanParams make_plan_params(const int32_t* cu, int32_t B, int32_t H, int3
   return p;
 }
 
-template <int THREADS>
+template <int THREADS, bool ORDER>
 struct PlanLds {
   int bins[kPlanBins];               // counts, then next position of the longest-first order
   int wave_sums[THREADS / 64];
@@ -52,11 +58,13 @@ struct PlanLds {
   int first[kPlanMaxChunks + 1];     // first position
   int item0[kPlanMaxChunks + 1];     // and first item
   int bad;
+  uint32_t order[ORDER ? kPlanMaxB : 1];  // ORDER: sequence | length << 13, by position
 };
+static_assert(kPlanMaxB == 1 << 13 && DORA_MAX_SEQLEN < 1 << 19, "order");
 
 // Called by every thread of a workgroup of THREADS.
-template <int THREADS>
-__device__ __forceinline__ void attn_plan_body(const PlanParams& p, PlanLds<THREADS>& s) {
+template <int THREADS, bool ORDER>
+__device__ __forceinline__ void attn_plan_body(const PlanParams& p, PlanLds<THREADS, ORDER>& s) {
   constexpr int kPer = kPlanBins / THREADS;  // bins per thread
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // Length bins: bin 0 for empty sequences, then (len - 1) >> shift + 1.
@@ -132,39 +140,58 @@ __device__ __forceinline__ void attn_plan_body(const PlanParams& p, PlanLds<THRE
   if (tid < 32) p.hdr->zero_row[tid] = 0u;
   __syncthreads();
 
-  // One lane per sequence where a sequence has few items; where it has more
-  // than 64 (long sequences), a wave writes those of its sequences one after
-  // the other, and the sequences are dealt over all waves.  One sequence of
-  // 16384 tokens with 12 heads: 41 us by one lane, 9.2 by a wave; groups of 16
-  // lanes for 12 items each took 143 us for 8192 sequences, a lane each 60.
-  const bool together = p.H * max_ch > 64;
-  const int b_first = together ? lane * (THREADS / 64) + wave : tid;
-  nlo = p.cu[min(b_first, p.B - 1)];
-  nhi = p.cu[min(b_first, p.B - 1) + 1];
+  // A sequence of few items is written by its lane, one of more than 64 (a long
+  // one) by its wave, and where there is such a one the sequences are dealt over
+  // all waves.  One sequence of 16384 tokens with 12 heads: 49 us by one lane, 10
+  // by a wave.  By the lengths, not by max_seqlen: 8192 sequences of 20 to 197
+  // tokens under max_seqlen 4096 took 263 us written by waves, 55 by lanes.
+  const bool ordered = ORDER && p.B > THREADS;
+  if (ordered) {
+    for (int b = tid; b < p.B; b += THREADS) {
+      const int len = p.cu[b + 1] - p.cu[b];
+      s.order[atomicAdd(&s.bins[bin_of(len)], 1)] = static_cast<uint32_t>(b) | (static_cast<uint32_t>(len) << 13);
+    }
+    __syncthreads();
+  }
+  const bool any_many = s.first[min(64 / p.H, max_ch)] > 0;
+  const int i_first = any_many ? lane * (THREADS / 64) + wave : tid;
+  int next_lo, next_len, next_pos = 0;
+  auto load = [&](int i) {  // past the last: the last again, as an empty one
+    const int at = min(i, p.B - 1);
+    if (ordered) {
+      next_pos = at;
+      next_len = static_cast<int>(s.order[at] >> 13);
+      next_lo = p.cu[s.order[at] & (kPlanMaxB - 1)];
+    } else {
+      next_lo = p.cu[at];
+      next_len = p.cu[at + 1] - next_lo;
+    }
+    if (i >= p.B) next_len = 0;
+  };
+  load(i_first);
 #pragma unroll 1
-  for (int b0 = 0; b0 < p.B; b0 += THREADS) {
-    const int b = b0 + b_first, nb = min(b + THREADS, p.B - 1);
-    const int lo = nlo, len = b < p.B ? nhi - nlo : 0;
-    nlo = p.cu[nb];
-    nhi = p.cu[nb + 1];
-    int pos = 0;
-    if (len > 0) pos = atomicAdd(&s.bins[bin_of(len)], 1);
-    if (together) {
-      for (uint64_t left = __ballot(len > 0); left != 0; left &= left - 1) {
-        const int l = __ffsll(static_cast<unsigned long long>(left)) - 1;
-        const int l_lo = __builtin_amdgcn_readlane(lo, l), l_len = __builtin_amdgcn_readlane(len, l);
-        const int ch = attn_chunks(l_len), groups = s.count[ch] * p.H, base = s.item0[ch];
-        const int g0 = (__builtin_amdgcn_readlane(pos, l) - s.first[ch]) * p.H;
-        for (int j = lane; j < p.H * ch; j += 64)
-          p.items[attn_item_slot(base, groups, ch, g0 + j / ch, j % ch)] = encode_item(l_lo, l_len, j / ch, j % ch);
-      }
-    } else if (len > 0) {
-      const int ch = attn_chunks(len), groups = s.count[ch] * p.H, base = s.item0[ch];
-      const int g0 = (pos - s.first[ch]) * p.H;
+  for (int i0 = 0; i0 < p.B; i0 += THREADS) {
+    const int lo = next_lo, len = next_len;
+    int pos = next_pos;
+    load(i0 + THREADS + i_first);
+    const int ch = attn_chunks(len);  // 0 for an empty sequence
+    const int groups = s.count[ch] * p.H, base = s.item0[ch];
+    if (!ordered && len > 0) pos = atomicAdd(&s.bins[bin_of(len)], 1);
+    const int g0 = (pos - s.first[ch]) * p.H;
+    const bool many = p.H * ch > 64;
+    for (uint64_t left = __ballot(many); left != 0; left &= left - 1) {
+      const int l = __ffsll(static_cast<unsigned long long>(left)) - 1;
+      const int l_lo = __builtin_amdgcn_readlane(lo, l), l_len = __builtin_amdgcn_readlane(len, l);
+      const int l_ch = attn_chunks(l_len), l_groups = s.count[l_ch] * p.H, l_base = s.item0[l_ch];
+      const int l_g0 = __builtin_amdgcn_readlane(g0, l);
+      for (int j = lane; j < p.H * l_ch; j += 64)
+        p.items[attn_item_slot(l_base, l_groups, l_ch, l_g0 + j / l_ch, j % l_ch)] =
+            encode_item(l_lo, l_len, j / l_ch, j % l_ch);
+    }
+    if (!many)
       for (int h = 0; h < p.H; ++h)
         for (int c = 0; c < ch; ++c)
           p.items[attn_item_slot(base, groups, ch, g0 + h, c)] = encode_item(lo, len, h, c);
-    }
   }
 }
 

@@ -561,8 +561,8 @@ __global__ __launch_bounds__(kThreads) void select_pack_kernel(SelectPackParams 
 // byte rows: a plan launch of its own took 55 us before a copy of 600.
 template <int SLOTS>
 __global__ __launch_bounds__(kThreads) void select_pack_planning_kernel(SelectPackParams p, PlanParams plan) {
-  __shared__ PlanLds<kThreads> lds;
-  if (blockIdx.x == 0) attn_plan_body<kThreads>(plan, lds);
+  __shared__ PlanLds<kThreads, false> lds;
+  if (blockIdx.x == 0) attn_plan_body<kThreads, false>(plan, lds);
   else select_pack_body<SLOTS, kCopy>(p, static_cast<int>(blockIdx.x) - 1);
 }
 

@@ -76,8 +76,8 @@ struct AttnParams {
 // ------------------------------- plan -------------------------------------
 
 __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(PlanParams p) {
-  __shared__ PlanLds<kPlanThreads> lds;
-  attn_plan_body<kPlanThreads>(p, lds);
+  __shared__ PlanLds<kPlanThreads, true> lds;
+  attn_plan_body<kPlanThreads, true>(p, lds);
 }
 
 // ------------------------------ execute -----------------------------------

@@ -303,6 +303,27 @@ def test_plan_edges(gpu, B, max_seqlen, H):
     assert_groups_share_a_subqueue(items)
 
 
+@pytest.mark.parametrize("B,long", [(64, 0), (64, 3), (1024, 0), (1024, 1), (1025, 0), (1025, 40), (5000, 0), (5000, 9)])
+def test_plan_short_sequences_under_a_large_bound(gpu, B, long):
+    """Short sequences, and a few long ones among them, where max_seqlen allows
+    long ones: items by lane and by wave, around the workgroup's size."""
+    rng = np.random.default_rng(B + long)
+    H, max_seqlen = 12, 4096
+    lens = rng.integers(0, 400, size=B).astype(np.int32)
+    lens[rng.permutation(B)[:long]] = rng.integers(961, max_seqlen + 1, size=long)   # more than 64 items each
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ws, st = gpu.new_workspace(B, H, max_seqlen), gpu.new_status()
+    gpu.dora_varlen_attn_plan(to_dev(cu), H, max_seqlen, int(cu[-1]), ws, st)
+    torch.cuda.synchronize()
+    hdr, n, items = read_plan(ws)
+    want = expected_items(lens, H, max_seqlen)
+    assert int(st.item()) == 0 and n == len(want)
+    assert np.all(hdr[32:64] == 0) and np.all(hdr[QUEUE_INTS + [EXIT_INT]] == 0)
+    assert np.all(np.diff([n_chunks(k) for k in (items[:, 1] >> 17)]) <= 0)
+    assert sorted(map(tuple, items.tolist())) == sorted(map(tuple, want.tolist()))
+    assert_groups_share_a_subqueue(items)
+
+
 @pytest.mark.parametrize("B,N", [(2049, 300), (2300, 20)])
 def test_plan_beside_the_copy(gpu, B, N):
     """Past 2048 images one workgroup of the copy launch makes the plan: rows
