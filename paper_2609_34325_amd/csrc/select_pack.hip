@@ -51,7 +51,8 @@ constexpr int kDigitSelectSlots = 8;  // rows of more than 256 tokens select by 
 // more than two per lane are left, two: 8192 images of 30 rows of 128 bytes 30.0
 // -> 29.0.
 constexpr int kCopyLoads = 8;
-// Workgroups that share an image: one per 32 KB of its kept rows (pick_split).
+// Workgroups that share an image: one per 32 KB, begun or whole, of its kept rows
+// (pick_split).
 constexpr int kPieceVecs = 2048;
 constexpr int kOrderGroup = 32;
 // Up to this many images each workgroup sums keep[0..b) itself (at most 8 KB
@@ -317,7 +318,7 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
   // for a few rows each.
   int split = p.split;
   if (split > p.fill_split) {
-    const long long pieces = (static_cast<long long>(kb) * p.row_vecs + kPieceVecs / 2) / kPieceVecs;
+    const long long pieces = (static_cast<long long>(kb) * p.row_vecs + kPieceVecs - 1) / kPieceVecs;
     split = static_cast<int>(min(max(pieces, static_cast<long long>(p.fill_split)), static_cast<long long>(split)));
     if (s >= split) return;  // s > 0: the image's first workgroup always stays
   }
@@ -658,11 +659,13 @@ hipError_t launch(const SelectPackParams& p, const PlanParams* plan, int mode, h
 // input's tokens per image (packed; N is only a bound there) and N.  By N alone:
 // 2048 packed images of 10 tokens with N = 2048 129 us, so 25; 1024 images of
 // which 12 of 197 tokens stay 22.6, so 8.8 (14 where the capacity does not say it and
-// the kernel leaves the workgroups out).
+// the kernel leaves the workgroups out).  A piece begun counts: with the nearest
+// number of pieces images that keep 32 to 48 KB had one workgroup (8192 of 38 KB
+// kept: 159 to 166 us, so 148), and none got faster.
 int pick_split(int B, int N, int64_t rows, int row_vecs, int* fill_split) {
   const int64_t max_split = std::max(N / 16, 1);  // at least ~16 rows per workgroup
   const int64_t fill = std::min<int64_t>((1024 + static_cast<int64_t>(B) - 1) / B, max_split);
-  int64_t split = std::max(fill, std::min({(rows * row_vecs + kPieceVecs / 2) / kPieceVecs, int64_t(8), max_split}));
+  int64_t split = std::max(fill, std::min({(rows * row_vecs + kPieceVecs - 1) / kPieceVecs, int64_t(8), max_split}));
   // A launch holds fewer than 2^32 threads, the plan's workgroup among them.
   while (split > 1 && (static_cast<int64_t>(B) * split + 1) * kThreads >= int64_t(1) << 32) --split;
   *fill_split = static_cast<int>(std::min(fill, split));
