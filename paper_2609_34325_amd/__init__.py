@@ -184,12 +184,13 @@ def _call(name: str, stream, *args) -> None:
     a negative status."""
     lib = _lib or load_library()
     which = _INDEX[name]
-    st = _stream(stream)
-    rc = _native_call(which, lib.addresses[which], *args, st)
+    rc = NotImplemented
+    if torch.cuda.is_initialized():  # else there is no tensor on the GPU
+        rc = _native_call(which, lib.addresses[which], *args, _stream(stream))
     if rc is NotImplemented:  # an argument that the native path leaves to these checks
         spec = _ENTRIES[which][1]
         rc = getattr(lib, name)(*(a if s is None or (a is None and s[0] in _OPTIONAL) else _dev(a, s[0], s[1])
-                                  for a, s in zip(args, spec)), st)
+                                  for a, s in zip(args, spec)), _stream(stream))
     if rc != DORA_OK:
         raise DoraError(name, rc)
 

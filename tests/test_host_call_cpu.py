@@ -3,6 +3,8 @@ argument lists, and the calls it leaves to the checks in Python."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -51,3 +53,24 @@ def test_left_to_python():
         dora._call("dora_actor_gate", 0, cpu, None, 4, 5, 3, cpu, cpu, cpu, cpu)
     with pytest.raises(TypeError, match="p_gate must be a torch tensor"):
         dora._call("dora_actor_gate", 0, None, None, 4, 5, 3, cpu, cpu, cpu, cpu)
+
+
+def test_arguments_are_checked_before_the_stream():
+    """Without a GPU a CPU tensor is what the error names, not the missing device."""
+    code = """
+import torch, paper_2609_34325_amd as dora
+st, scores, keep = torch.zeros(1, dtype=torch.int32), torch.zeros(2, 5), torch.ones(2, dtype=torch.int32)
+for call, name in ((lambda: dora.dora_select_pack(scores, keep, torch.zeros(2, 5, 8), cap_rows=2, dev_status=st), "scores"),
+                   (lambda: dora.dora_actor_gate(torch.zeros(2), 1, 5, dev_status=st), "p_gate"),
+                   (lambda: dora.dora_varlen_attn_plan(torch.zeros(3, dtype=torch.int32), 1, 5, 5, scores, st), "cu_seqlens")):
+    try:
+        call()
+    except ValueError as e:
+        assert str(e) == name + " must be on the GPU", e
+    else:
+        raise AssertionError(name)
+assert not torch.cuda.is_initialized()
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="", CUDA_VISIBLE_DEVICES="")
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr
