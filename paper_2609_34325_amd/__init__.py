@@ -18,13 +18,13 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdora.so")
-HOST_PATH = os.path.join(_HERE, "_host_call.so")
 
 DORA_F32 = 0
 DORA_BF16 = 1
@@ -119,6 +119,10 @@ class DoraError(RuntimeError):
         self.code = code
 
 
+def _leave_to_ctypes(*args):
+    return NotImplemented
+
+
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     """Load libdora.so (built in-tree by ``paper_2609_34325_amd.build``)."""
     global _lib, _native_call
@@ -169,10 +173,12 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.dora_status_string.argtypes = [ctypes.c_int]
     lib.addresses = tuple(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name, _ in _ENTRIES)
     if _native_call is None:
-        if not os.path.exists(HOST_PATH):
-            raise RuntimeError(f"{HOST_PATH} not found; build it with `python -m paper_2609_34325_amd.build`")
-        from . import _host_call
-        _native_call = _host_call.call
+        try:
+            from ._host_call import call as _native_call
+        except ImportError as e:  # not built, or for another Python or torch
+            warnings.warn(f"calls are marshalled by ctypes, about 5 us slower each: {e}; build the native marshalling "
+                          "with `python -m paper_2609_34325_amd.build`")
+            _native_call = _leave_to_ctypes
     if path is None:
         _lib = lib
     return lib

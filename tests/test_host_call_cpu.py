@@ -55,6 +55,36 @@ def test_left_to_python():
         dora._call("dora_actor_gate", 0, None, None, 4, 5, 3, cpu, cpu, cpu, cpu)
 
 
+def test_built():
+    """The native marshalling itself is what the other tests run through."""
+    dora.load_library()
+    assert dora._native_call is not None and dora._native_call is not dora._leave_to_ctypes
+
+
+def test_library_loads_without_the_native_marshalling():
+    """Not built, or built for another Python or torch: calls go through ctypes."""
+    code = """
+import sys, warnings
+sys.modules["paper_2609_34325_amd._host_call"] = None
+import torch, paper_2609_34325_amd as dora
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    lib = dora.load_library()
+assert [w for w in seen if "ctypes" in str(w.message)]
+i = dora._INDEX["dora_actor_gate"]
+assert dora._native_call(i, lib.addresses[i], 1) is NotImplemented
+assert dora.dora_status_string(0) == "DORA_OK"
+try:
+    dora._call("dora_actor_gate", 0, torch.zeros(4), None, 4, 5, 3, *[torch.zeros(4)] * 4)
+except ValueError as e:
+    assert str(e) == "p_gate must be on the GPU"
+else:
+    raise AssertionError
+"""
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr
+
+
 def test_arguments_are_checked_before_the_stream():
     """Without a GPU a CPU tensor is what the error names, not the missing device."""
     code = """
