@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -57,6 +58,8 @@ def build(verbose: bool = False) -> str:
 
 
 def _build_host(verbose: bool) -> None:
+    """Needs a host compiler and torch's C++ headers; without them the binding
+    goes through ctypes."""
     import sysconfig
 
     import torch
@@ -71,10 +74,18 @@ def _build_host(verbose: bool) -> None:
            "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("host build failed:\n" + res.stdout + res.stderr)
-    os.replace(tmp, HOST_LIB)
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        failed = res.stdout + res.stderr if res.returncode != 0 else None
+    except OSError as e:  # no such compiler
+        failed = str(e)
+    if failed is None:
+        os.replace(tmp, HOST_LIB)
+        return
+    for path in (tmp, HOST_LIB):  # one of an earlier build may not fit the library's present arguments
+        if os.path.exists(path):
+            os.remove(path)
+    warnings.warn("the native marshalling was not built, calls will go through ctypes:\n" + failed)
 
 
 def _build_one(sources, lib: str, verbose: bool) -> None:

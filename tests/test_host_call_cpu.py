@@ -85,6 +85,19 @@ else:
     assert res.returncode == 0, res.stderr
 
 
+@pytest.mark.parametrize("cxx", ["false", "/no/such/compiler"])
+def test_build_without_a_host_compiler(tmp_path, monkeypatch, cxx):
+    """The library needs hipcc only; an older marshalling does not stay behind."""
+    from paper_2609_34325_amd import build
+    host = tmp_path / "_host_call.so"
+    host.write_bytes(b"old")
+    monkeypatch.setattr(build, "HOST_LIB", str(host))
+    monkeypatch.setenv("CXX", cxx)
+    with pytest.warns(UserWarning, match="ctypes"):
+        build._build_host(False)
+    assert not list(tmp_path.iterdir())
+
+
 def test_arguments_are_checked_before_the_stream():
     """Without a GPU a CPU tensor is what the error names, not the missing device."""
     code = """
