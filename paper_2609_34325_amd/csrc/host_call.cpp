@@ -25,8 +25,8 @@ union Arg {
   float f;
 };
 
-// Argument kinds: F, I, L, U, A are float32, int32, int64, uint8 and any-type
-// tensors (lower case: or None), n an integer, e a float, s an address.
+// Argument kinds: F, I, L, A are float32, int32, int64 and any-type tensors
+// (lower case: or None), n an integer, e a float, s an address.
 struct Entry {
   const char* kinds;
   int (*call)(void* fn, const Arg* a);
@@ -36,7 +36,7 @@ template <class T>
 T* ptr(const Arg& a) {
   return static_cast<T*>(a.p);
 }
-// The entry point of `like`'s type at address fn (the loaded library's).
+// The entry point of the declared function's type at address fn (the loaded library's).
 template <class F>
 F* at_address(F&, void* fn) {
   return reinterpret_cast<F*>(fn);
@@ -159,15 +159,26 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         Py_RETURN_NOTIMPLEMENTED;
       }
     }
-    // A launch can wait for room in its queue: let other threads run, as ctypes does.
-    int rc = 0;
-    Py_BEGIN_ALLOW_THREADS
-    rc = entry.call(fn, a);
-    Py_END_ALLOW_THREADS
-    return PyLong_FromLong(rc);
   } catch (...) {
     Py_RETURN_NOTIMPLEMENTED;
   }
+  // A launch can wait for room in its queue: let other threads run, as ctypes
+  // does.  What an entry point throws is caught where the GIL is not held, and
+  // the call is not made again.
+  int rc = 0;
+  bool threw = false;
+  Py_BEGIN_ALLOW_THREADS
+  try {
+    rc = entry.call(fn, a);
+  } catch (...) {
+    threw = true;
+  }
+  Py_END_ALLOW_THREADS
+  if (threw) {
+    PyErr_SetString(PyExc_RuntimeError, "the entry point threw a C++ exception");
+    return nullptr;
+  }
+  return PyLong_FromLong(rc);
 }
 
 PyMethodDef kMethods[] = {
