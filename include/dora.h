@@ -423,7 +423,10 @@ int dora_trajectory_flops(const int32_t* tokens, int32_t B, const dora_flops_con
  *              to bf16 for the P.V product, output rounded once to bf16.
  *              DORA_F32: fp32 throughout (products from three-term bf16
  *              splits of the operands, to within 2^-26; infinities and NaN as
- *              in fp32 arithmetic).
+ *              in fp32 arithmetic).  While three workgroups per item fit the
+ *              GPU, by B, H and max_seqlen, an item's keys are summed in three
+ *              parts, so the last bits of a sequence's fp32 result can differ
+ *              between a small and a large batch.
  *   workspace  as filled by dora_varlen_attn_plan (or dora_select_pack_plan)
  *              with the same cu_seqlens, B, H, max_seqlen and total; otherwise
  *              DORA_DEV_PLAN is set and nothing is written.
