@@ -51,9 +51,12 @@ constexpr int kDigitSelectSlots = 8;  // rows of more than 256 tokens select by 
 // more than two per lane are left, two: 8192 images of 30 rows of 128 bytes 30.0
 // -> 29.0.
 constexpr int kCopyLoads = 8;
-// Workgroups that share an image: one per 32 KB, begun or whole, of its kept rows
-// (pick_split).
-constexpr int kPieceVecs = 2048;
+// Workgroups that share an image: one per piece, begun or whole, of its kept rows
+// (pick_split).  24 KB, and 32 where all four waves select (the selection that each
+// workgroup repeats costs more).  With 32 instead of 24: 8192 images of 197 rows of
+// 1536 bytes, half kept, 480 us against 459, 1024 55.5 and 54.4; with 24 instead of
+// 32: 2048 images of 577 rows of 384 bytes, half kept, 96 against 93.
+__host__ __device__ constexpr int piece_vecs(bool wide) { return wide ? 2048 : 1536; }
 constexpr int kOrderGroup = 32;
 // Up to this many images each workgroup sums keep[0..b) itself (at most 8 KB
 // of keep counts from the L2, cheaper than a second launch); above it one
@@ -71,6 +74,7 @@ struct SelectPackParams {
   int64_t total_in;
   int32_t B, N, row_vecs, split;
   int32_t fill_split;  // workgroups per image that take part however few rows it keeps
+  uint32_t split_inv;  // 2^32 / split rounded up, for block / split
   int32_t* idx_out;
   int32_t* cu_out;
   uint4* packed;
@@ -288,16 +292,15 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
   // by side, the ones that take no part would leave whole XCDs idle (1024 images
   // of 577 tokens, 50 of them kept: 55 to 101 us, so 33).
   int b = block, s = 0;
-  if (p.split == p.fill_split) {
-    if (p.split > 1) {
-      b = block / p.split;
-      s = block - b * p.split;
+  if (p.split > 1) {
+    b = static_cast<int>(__umulhi(static_cast<uint32_t>(block), p.split_inv));  // block / split (pick_split)
+    s = block - b * p.split;
+    const int first = b & -kOrderGroup;
+    if (p.split > p.fill_split && first + kOrderGroup <= p.B) {
+      const int i = block - first * p.split;
+      s = i / kOrderGroup;
+      b = first + i % kOrderGroup;
     }
-  } else {
-    const int first = block / (kOrderGroup * p.split) * kOrderGroup, i = block - first * p.split;
-    const int images = min(kOrderGroup, p.B - first);
-    s = images == kOrderGroup ? i / kOrderGroup : i / images;
-    b = first + i - s * images;
   }
 
   // Segment of image b in the input.
@@ -314,12 +317,13 @@ __device__ __forceinline__ void select_pack_body(const SelectPackParams& p, int 
   }
   const int kb = p.keep[b];
   // Workgroups that take part: of those that the image's size has brought, one per
-  // kPieceVecs of the rows that are kept; the others would repeat the selection
+  // piece of the rows that are kept; the others would repeat the selection
   // for a few rows each.
   int split = p.split;
   if (split > p.fill_split) {
-    const long long pieces = (static_cast<long long>(kb) * p.row_vecs + kPieceVecs - 1) / kPieceVecs;
-    split = static_cast<int>(min(max(pieces, static_cast<long long>(p.fill_split)), static_cast<long long>(split)));
+    constexpr int kPiece = piece_vecs(kWide);
+    const int pieces = (min(max(kb, 0), p.N) * p.row_vecs + kPiece - 1) / kPiece;  // at most 2^27 vectors
+    split = min(max(pieces, p.fill_split), split);
     if (s >= split) return;  // s > 0: the image's first workgroup always stays
   }
   const long long cu_b = p.cu_ready ? static_cast<long long>(p.cu_out[b]) : 0;
@@ -647,21 +651,20 @@ hipError_t launch(const SelectPackParams& p, const PlanParams* plan, int mode, h
 }
 
 // Workgroups per image: enough for the batch to fill the chip (about 4 per
-// compute unit: *fill_split), and one per 32 KB of kept rows, at most 8, so that
+// compute unit: *fill_split), and one per piece of kept rows, at most 8, so that
 // the selection of one workgroup runs under the copies of others and the last
 // round of workgroups is short.  More cost more than they give, since each
 // repeats the selection.  Cold inputs, 1 / 2 / 4 / 6 / 8 workgroups per image, half of the rows kept:
 // 8192 images of 303 KB 675 / 659 / 642 / 602 / 608 us, 1024 of 303 KB 92.6 /
 // 87.4 / 81.1 / 78.8 / 78.2, 256 of 886 KB 72.7 / 71.9 / 68.7 / 68.6 / 66.5, 8192 of
-// 76 KB 171 / 157 / 180 / 250 / 323, 4096 of 25 KB 33.5 / 41.2 / 65.  (24 KB: 8192 of
-// 303 KB 2 % faster, 256 of 303 KB 6 % slower.)  `rows`: what the
+// 76 KB 171 / 157 / 180 / 250 / 323, 4096 of 25 KB 33.5 / 41.2 / 65.  `rows`: what the
 // host knows of an image's kept rows: at most the output's capacity per image, the
 // input's tokens per image (packed; N is only a bound there) and N.  By N alone:
 // 2048 packed images of 10 tokens with N = 2048 129 us, so 25; 1024 images of
 // which 12 of 197 tokens stay 22.6, so 8.8 (14 where the capacity does not say it and
 // the kernel leaves the workgroups out).  A piece begun counts: with the nearest
-// number of pieces images that keep 32 to 48 KB had one workgroup (8192 of 38 KB
-// kept: 159 to 166 us, so 148), and none got faster.
+// number of pieces of 32 KB, images that keep 32 to 48 had one workgroup (8192 of 38 KB
+// kept: 159 to 166 us, so 148), and no size was faster for it.
 // `bound`: the rows are no more than a bound (the capacity is not below the
 // input's rows).  A small batch, a launch of a few us, then takes half of them as
 // kept: a workgroup that leaves costs about 1 ns (256 images that keep 20 or 60 of
@@ -672,7 +675,8 @@ int pick_split(int B, int N, int64_t rows, bool bound, int row_vecs, int* fill_s
   const int64_t max_split = std::max(N / 16, 1);  // at least ~16 rows per workgroup
   const int64_t fill = std::min<int64_t>((1024 + static_cast<int64_t>(B) - 1) / B, max_split);
   if (bound && fill >= 4) rows = (rows + 1) / 2;
-  int64_t split = std::max(fill, std::min({(rows * row_vecs + kPieceVecs - 1) / kPieceVecs, int64_t(8), max_split}));
+  const int piece = piece_vecs(N > 256);
+  int64_t split = std::max(fill, std::min({(rows * row_vecs + piece - 1) / piece, int64_t(8), max_split}));
   // A launch holds fewer than 2^32 threads, the plan's workgroup among them.
   while (split > 1 && (static_cast<int64_t>(B) * split + 1) * kThreads >= int64_t(1) << 32) --split;
   *fill_split = static_cast<int>(std::min(fill, split));
@@ -706,6 +710,8 @@ int prepare(const float* scores, const int32_t* keep, const void* tokens, const 
   const int64_t in_rows = cu_in != nullptr ? std::min<int64_t>(N, (total_in + B - 1) / B) : N;
   const int64_t cap_per_image = (cap_rows + B - 1) / B;
   p->split = pick_split(B, N, std::min(in_rows, cap_per_image), cap_per_image >= in_rows, p->row_vecs, &p->fill_split);
+  // Exact for every block: a launch has fewer than 2^24, a split of at most 8 unless it is one of 2048 and less.
+  p->split_inv = static_cast<uint32_t>(((int64_t(1) << 32) + p->split - 1) / p->split);
   p->idx_out = idx_out;
   p->cu_out = cu_out;
   p->packed = static_cast<uint4*>(packed_out);
