@@ -834,12 +834,15 @@ __global__ __launch_bounds__(kThreads) void attn_fwd_bf16_kernel(AttnParams p) {
 // waves take 32 keys of a stage each, so a workgroup's chain of products is a
 // third as long; their partial results meet in LDS at the end.
 //
-// What bounds it: per 16 queries and 64 keys 96 matrix instructions (1536
-// cycles) and about 210 VALU ones (1050 cycles), of which the three waves of a
-// SIMD overlap about a fifth; at short sequences also the start of each item.
+// What bounds it (counters at 64 sequences of 577 tokens with 12 heads): per 16
+// queries and 64 keys 96 matrix instructions (1536 cycles of a SIMD) and 400 VALU
+// ones (1600: exponentials, the splits of P and of the staged K and V, item starts),
+// which the three waves of a SIMD overlap little: 3850 cycles; the waves wait
+// in 41 % of theirs.  No LDS bank conflicts.
 // Kernel times with fp32 matrix instructions -> now (12 heads, graph replays):
-// 64 sequences of 136 tokens 87.9 -> 37.5 us, 256 of 197 538 -> 284, 64 of
-// 577 842 -> 414; 3 heads: one of 4096 191 -> 124, 4 of 197 17.8 -> 12.2.
+// 64 sequences of 136 tokens 88.0 -> 43.3 us, 256 of 197 539 -> 325, 64 of
+// 577 838 -> 431, 2048 of 17 852 -> 358; 3 heads: one of 4096 191 -> 128, 4 of 197
+// 17.7 -> 12.2.
 // Largest error against 64 bits at 136 to 4000 tokens, relative in the
 // 2-norm: 3.4e-7 .. 9.2e-7 -> 1.3e-7 .. 2.1e-7.
 // ---------------------------------------------------------------------------
@@ -1018,8 +1021,8 @@ __device__ __forceinline__ void f32_block(const char* Ks, const char* Vs, LdsOff
 // instructions of 32 cycles per 16 keys; more loads in flight would take registers
 // from the key loop of the kernel it is part of, which then spills.  Whole pass on
 // NaN inputs, one load at a time -> now (fp32 matrix instructions for every tile
-// from the start): 64 sequences of 136 tokens with 12 heads 320 -> 116 us (94), 64
-// of 577 4882 -> 1525 (838), one of 4096 with 3 heads 1851 -> 522 (190).
+// from the start): 64 sequences of 136 tokens with 12 heads 318 -> 104 us (88), 64
+// of 577 4940 -> 1524 (839), one of 4096 with 3 heads 1838 -> 520 (189).
 __device__ __forceinline__ void f32_tile_direct(const AttnParams& p, long long seq0, int len, int h, int q0, int qend) {
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));  // addresses are formed here, not ahead of the caller's key loop
