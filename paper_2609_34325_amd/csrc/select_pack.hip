@@ -51,11 +51,12 @@ constexpr int kDigitSelectSlots = 8;  // rows of more than 256 tokens select by 
 // more than two per lane are left, two: 8192 images of 30 rows of 128 bytes 30.0
 // -> 29.0.
 constexpr int kCopyLoads = 8;
-// Workgroups that share an image: one per piece, begun or whole, of its kept rows
-// (pick_split).  24 KB, and 32 where all four waves select (the selection that each
-// workgroup repeats costs more).  With 32 instead of 24: 8192 images of 197 rows of
-// 1536 bytes, half kept, 480 us against 459, 1024 55.5 and 54.4; with 24 instead of
-// 32: 2048 images of 577 rows of 384 bytes, half kept, 96 against 93.
+// Large batches: workgroups that share an image, one per piece, begun or whole, of
+// its kept rows (pick_split).  24 KB, and 32 where all four waves select (the
+// selection that each workgroup repeats costs more).  With 32 instead of 24: 8192
+// images of 197 rows of 1536 bytes, half kept, 480 us against 459, 1024 55.5 and
+// 54.4; with 24 instead of 32: 2048 images of 577 rows of 384 bytes, half kept, 96
+// against 93.
 __host__ __device__ constexpr int piece_vecs(bool wide) { return wide ? 2048 : 1536; }
 constexpr int kOrderGroup = 32;
 // Up to this many images each workgroup sums keep[0..b) itself (at most 8 KB
@@ -650,37 +651,44 @@ hipError_t launch(const SelectPackParams& p, const PlanParams* plan, int mode, h
   return hipGetLastError();
 }
 
-// Workgroups per image: enough for the batch to fill the chip (about 4 per
-// compute unit: *fill_split), and one per piece of kept rows, at most 8, so that
-// the selection of one workgroup runs under the copies of others and the last
-// round of workgroups is short.  More cost more than they give, since each
-// repeats the selection.  Cold inputs, 1 / 2 / 4 / 6 / 8 workgroups per image, half of the rows kept:
-// 8192 images of 303 KB 675 / 659 / 642 / 602 / 608 us, 1024 of 303 KB 92.6 /
-// 87.4 / 81.1 / 78.8 / 78.2, 256 of 886 KB 72.7 / 71.9 / 68.7 / 68.6 / 66.5, 8192 of
-// 76 KB 171 / 157 / 180 / 250 / 323, 4096 of 25 KB 33.5 / 41.2 / 65.  `rows`: what the
-// host knows of an image's kept rows: at most the output's capacity per image, the
-// input's tokens per image (packed; N is only a bound there) and N.  By N alone:
-// 2048 packed images of 10 tokens with N = 2048 129 us, so 25; 1024 images of
-// which 12 of 197 tokens stay 22.6, so 8.8 (14 where the capacity does not say it and
-// the kernel leaves the workgroups out).  A piece begun counts: with the nearest
-// number of pieces of 32 KB, images that keep 32 to 48 had one workgroup (8192 of 38 KB
-// kept: 159 to 166 us, so 148), and no size was faster for it.
-// `bound`: the rows are no more than a bound (the capacity is not below the
-// input's rows).  A small batch, a launch of a few us, then takes half of them as
-// kept: a workgroup that leaves costs about 1 ns (256 images that keep 20 or 60 of
-// 197 rows of 1536 bytes 8.2 and 9.5 us, so 7.2 and 8.5; 256 that keep 14 to 197
-// unchanged).  Larger batches whose images differ gain from the workgroups more
-// (4096 images, half of them hardly pruned: 129 us, with half 141).
-int pick_split(int B, int N, int64_t rows, bool bound, int row_vecs, int* fill_split) {
+// Workgroups per image, so that the selection of one runs under the copies of
+// others and the last round of workgroups is short.  More cost more than they give,
+// since each repeats the selection.  Cold inputs, 1 / 2 / 4 / 6 / 8 workgroups per
+// image, half of the rows kept: 8192 images of 303 KB 675 / 659 / 642 / 602 / 608 us,
+// 1024 of 303 KB 92.6 / 87.4 / 81.1 / 78.8 / 78.2, 256 of 886 KB 72.7 / 71.9 / 68.7 /
+// 68.6 / 66.5, 8192 of 76 KB 171 / 157 / 180 / 250 / 323, 4096 of 25 KB 33.5 / 41.2 /
+// 65.  What the host knows of an image's rows: at most N, the input's tokens per
+// image (in_rows; packed, where N is only a bound), and the output's capacity per
+// image (cap_rows).
+//
+// Below 1024 images: enough for the batch to fill the chip (about 4 per compute
+// unit), or one per 48 KB of the image's rows (of twice the capacity, where that is
+// less), at most 8, and all take part.  By the kept rows as below, 600 images of 197
+// rows of 1536 bytes, half of them hardly pruned, took 44.7 us against 43.0, 200 of
+// 577 with 10 to 100 % kept 49.0 against 46.7.
+//
+// From 1024 on: one per piece of the rows that the host knows may be kept, at most
+// 8, of which the kernel lets those take part that an image's own kept rows ask for
+// (*fill_split, here 1, always do).  By N alone: 2048 packed images of 10 tokens with
+// N = 2048 129 us, so 25; 1024 images of which 12 of 197 tokens stay 22.6, so 8.8 (11.4
+// where the capacity does not say it and workgroups leave).  A piece begun counts:
+// with the nearest number of pieces of 32 KB, images that keep 32 to 48 had one
+// workgroup (8192 of 38 KB kept: 159 to 166 us, so 148), and no size was faster for it.
+int pick_split(int B, int N, int64_t in_rows, int64_t cap_rows, int row_vecs, int* fill_split) {
   const int64_t max_split = std::max(N / 16, 1);  // at least ~16 rows per workgroup
   const int64_t fill = std::min<int64_t>((1024 + static_cast<int64_t>(B) - 1) / B, max_split);
-  if (bound && fill >= 4) rows = (rows + 1) / 2;
+  if (fill > 1) {
+    constexpr int64_t kPart = 3072;  // 48 KB
+    const int64_t parts = (std::min(in_rows, 2 * cap_rows) * row_vecs + kPart / 2) / kPart;
+    *fill_split = static_cast<int>(std::min(std::max(fill, std::min<int64_t>(parts, 8)), max_split));
+    return *fill_split;
+  }
   const int piece = piece_vecs(N > 256);
-  int64_t split = std::max(fill, std::min({(rows * row_vecs + piece - 1) / piece, int64_t(8), max_split}));
+  int64_t split = std::min({(std::min(in_rows, cap_rows) * row_vecs + piece - 1) / piece, int64_t(8), max_split});
   // A launch holds fewer than 2^32 threads, the plan's workgroup among them.
   while (split > 1 && (static_cast<int64_t>(B) * split + 1) * kThreads >= int64_t(1) << 32) --split;
-  *fill_split = static_cast<int>(std::min(fill, split));
-  return static_cast<int>(split);
+  *fill_split = 1;
+  return static_cast<int>(std::max<int64_t>(split, 1));
 }
 
 // Checks the arguments of a select/pack call and fills `p` (no plan).
@@ -708,8 +716,7 @@ int prepare(const float* scores, const int32_t* keep, const void* tokens, const 
   p->row_vecs = static_cast<int32_t>(row_bytes / 16);
   // Rows an image keeps, on average, as far as the host knows.
   const int64_t in_rows = cu_in != nullptr ? std::min<int64_t>(N, (total_in + B - 1) / B) : N;
-  const int64_t cap_per_image = (cap_rows + B - 1) / B;
-  p->split = pick_split(B, N, std::min(in_rows, cap_per_image), cap_per_image >= in_rows, p->row_vecs, &p->fill_split);
+  p->split = pick_split(B, N, in_rows, (cap_rows + B - 1) / B, p->row_vecs, &p->fill_split);
   // Exact for every block: a launch has fewer than 2^24, a split of at most 8 unless it is one of 2048 and less.
   p->split_inv = static_cast<uint32_t>(((int64_t(1) << 32) + p->split - 1) / p->split);
   p->idx_out = idx_out;
