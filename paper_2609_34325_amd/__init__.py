@@ -192,7 +192,8 @@ def _call(name: str, stream, *args) -> None:
     which = _INDEX[name]
     rc = NotImplemented
     if torch.cuda.is_initialized():  # else there is no tensor on the GPU
-        rc = _native_call(which, lib.addresses[which], *args, _stream(stream))
+        st = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if stream is None else _stream(stream)
+        rc = _native_call(which, lib.addresses[which], *args, st)
     if rc is NotImplemented:  # an argument that the native path leaves to these checks
         spec = _ENTRIES[which][1]
         rc = getattr(lib, name)(*(a if s is None or (a is None and s[0] in _OPTIONAL) else _dev(a, s[0], s[1])
@@ -226,9 +227,8 @@ def _dev(t: torch.Tensor, name: str, dtype=None) -> int:
 
 
 def _stream(stream) -> int:
-    if stream is None:  # the current device's current stream
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if torch.cuda.is_initialized() else \
-            torch.cuda.current_stream().cuda_stream
+    if stream is None:
+        return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
